@@ -70,7 +70,8 @@ def workload(name):
 
 # Sources the collide kernel is compiled from: a traffic figure measured with
 # hardware counters holds only while these are unchanged.
-COLLIDE_SOURCES = ("paper_2102_01305_amd/csrc/collide.hip", "paper_2102_01305_amd/csrc/lattice_dev.h",
+COLLIDE_SOURCES = ("paper_2102_01305_amd/csrc/collide.hip", "paper_2102_01305_amd/csrc/pair.hip",
+                   "paper_2102_01305_amd/csrc/update_dev.h", "paper_2102_01305_amd/csrc/lattice_dev.h",
                    "paper_2102_01305_amd/csrc/internal.h")
 
 
@@ -304,9 +305,13 @@ def timed_solve(wname, storage, steps, warmup, timing_every):
     nl = tim["collide_launches"]
     k6_ms = tim["collide_ms"] / nl if nl else float("nan")
     cells_per_launch = tim["collide_cells"] / nl if nl else float("nan")
-    achieved = bpc * cells_per_launch / (k6_ms * 1e-3) / 1e9 if nl else float("nan")
+    # a launch that takes two steps in one pass updates every cell twice, but
+    # reads and writes the lattice once
+    per_launch = cells_per_launch / N if nl else 1.0
+    achieved = bpc * N / (k6_ms * 1e-3) / 1e9 if nl else float("nan")
     fig = dict(N=N, dt=dt, mlups=mlups, bpc=bpc, k6_ms=k6_ms, cells_per_launch=cells_per_launch,
-               achieved=achieved, launches=nl, marker_ms=tim["marker_ms"] / max(nl, 1))
+               achieved=achieved, launches=nl, steps_per_launch=per_launch,
+               marker_ms=tim["marker_ms"] / max(nl * per_launch, 1))
     return name, bx, wg, ph, u0, rho0, fig
 
 
@@ -369,7 +374,8 @@ def main():
                    "wings": len(wg)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                     "kernel": "k_collide", "kernel_ms": round(k6_ms, 5),
+                     "kernel": "k_pair" if fig["steps_per_launch"] > 1.5 else "k_collide",
+                     "steps_per_launch": round(fig["steps_per_launch"], 3), "kernel_ms": round(k6_ms, 5),
                      "bytes_per_cell": bpc, "cells_per_launch": cells_per_launch,
                      "timed_launches": fig["launches"],
                      "marker_ms_per_step": round(fig["marker_ms"], 5),
@@ -384,6 +390,7 @@ def main():
             vn, _, _, _, _, _, vf = timed_solve(wv, sv_, kv, wu, args.timing_every)
             var.append({"workload": vn, "storage": sv_, "steps": kv, "value": round(vf["mlups"], 1),
                         "ms_per_step": round(vf["dt"] / kv * 1e3, 5),
+                        "steps_per_launch": round(vf["steps_per_launch"], 3),
                         "kernel_ms": round(vf["k6_ms"], 5), "achieved": round(vf["achieved"], 1),
                         "frac": round(vf["achieved"] / HBM_PEAK_GBS, 4),
                         "traffic": measured_traffic(vn, sv_),

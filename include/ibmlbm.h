@@ -183,7 +183,9 @@ IBMLBM_API int ibmlbm_set_kinematics(ibmlbm_t h, int32_t n_wings, const ibmlbm_w
 
 /* Enqueue n time steps (Sec. 2.2): streaming, moments, marker kinematics at
  * t = step, interpolation, the no-slip solve A X = B (Eq. 19, minimum-norm
- * solution), spreading, Guo-forced collision and force integration. */
+ * solution), spreading, Guo-forced collision and force integration.  Where it
+ * is the faster way the lattice takes two of the n steps in one pass; the
+ * results are those of single steps, bit for bit, however n is portioned. */
 IBMLBM_API int ibmlbm_step(ibmlbm_t h, int32_t n);
 
 /* Enqueue n time steps of each of n_handles solves (1..64 distinct,
@@ -247,8 +249,11 @@ IBMLBM_API int ibmlbm_mass(ibmlbm_t h, int64_t* step, double* mass);
 
 /* Kernel timing: with enable = k > 0 the collide-stream launch and the
  * marker kernels of every k-th step are bracketed by HIP events (recorded
- * without a system-scope fence) on the handle's stream; read_timing
- * synchronises, returns the summed milliseconds, count and updated cells of
+ * without a system-scope fence) on the handle's stream (both steps of a pair
+ * taken in one pass, if either is due: that launch updates every cell twice,
+ * and the update of the cells around the foils ahead of it counts with the
+ * markers); read_timing
+ * synchronises, returns the summed milliseconds, count and cell updates of
  * the bracketed collide launches and the summed marker milliseconds, and
  * resets the sums.  enable = 0 stops recording. */
 IBMLBM_API int ibmlbm_timing(ibmlbm_t h, int32_t enable);

@@ -11,7 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libibmlbm.so")
-SOURCES = ["collide.hip", "markers.hip", "scratch.hip", "api.cpp"]
+SOURCES = ["collide.hip", "pair.hip", "markers.hip", "scratch.hip", "api.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

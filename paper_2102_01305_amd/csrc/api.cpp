@@ -98,6 +98,7 @@ struct ibmlbm_s {
   // timing
   bool timing = false;
   int timing_every = 1;             // bracket one step in this many
+  bool time_this = false;           // the step (or pair) being enqueued is bracketed
   std::vector<hipEvent_t> ev;       // pairs: start, stop
   std::vector<int> ev_kind;         // 0 = collide, 1 = markers
   size_t ev_used = 0;
@@ -637,10 +638,20 @@ int fold_events(ibmlbm_t h) {
   return IBMLBM_OK;
 }
 
+// Whether the step being enqueued is bracketed by timing events; both steps
+// of a pair are if either is due.
+void time_step(ibmlbm_t h, bool first, bool second) {
+  const int e = h->timing_every;
+  if (!h->timing)
+    h->time_this = false;
+  else if (!second)
+    h->time_this = h->step % e == 0 || (first && (h->step + 1) % e == 0);
+}
+
 // Timing event on stream `st` for the step being enqueued (kind 0: a
 // collide launch updating `cells` cells, kind 1: the marker kernels).
 int record_event(ibmlbm_t h, hipStream_t st, int kind, bool start, double cells = 0.0) {
-  if (!h->timing || h->step % h->timing_every != 0) return IBMLBM_OK;
+  if (!h->time_this) return IBMLBM_OK;
   if (start) {
     if (h->ev_used + 2 > h->ev.size()) {
       HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -655,12 +666,11 @@ int record_event(ibmlbm_t h, hipStream_t st, int kind, bool start, double cells 
   return IBMLBM_OK;
 }
 
-// Arguments of step s whose current state is A if cur_A: the parts that
-// never change for this handle, then the step's own (state buffers, time,
-// window slot, force-history row, node boxes and the grids they imply).
+// Arguments of step s: the parts that
+// never change for this handle, then the step's own (time, window slot, force-history row, node boxes and the grids they imply).
 const void* dev_ma(ibmlbm_t h, int slot);
 
-void step_args(ibmlbm_t h, long long s, bool cur_A, CollideArgs& ca, MarkerArgs& ma) {
+void step_args(ibmlbm_t h, long long s, CollideArgs& ca, MarkerArgs& ma) {
   const LatticeLayout& L = h->L;
   const ibmlbm_config& c = h->cfg;
   ca = CollideArgs{};
@@ -679,10 +689,6 @@ void step_args(ibmlbm_t h, long long s, bool cur_A, CollideArgs& ca, MarkerArgs&
   ca.ny_mul = div_mul(c.ny, (unsigned long long)c.ny * c.nz);
   ca.mass_part = at<double>(h, L.mass_part);
   ca.flags = reinterpret_cast<int*>(h->sb + L.diag.off + 16);
-  void* A = h->ws + L.fA.off;
-  void* B = h->ws + L.fB.off;
-  ca.src = cur_A ? A : B;
-  ca.dst = cur_A ? B : A;
   if (h->nw == 0) return;
   ma.g = h->geo;
   ma.p = h->phys;
@@ -720,7 +726,6 @@ void step_args(ibmlbm_t h, long long s, bool cur_A, CollideArgs& ca, MarkerArgs&
     double* q = ma.pose[k];
     wing_pose(ma.w[k], (double)s, q[0], q[1], q[2], q[3], q[4], q[5]);
   }
-  ma.src = ca.src;
   ca.hist_row = s % c.history_steps;
   long long band_waves = 0;
   int maxnp = 0, maxcells = 0;
@@ -766,7 +771,7 @@ int fill_window(ibmlbm_t h, long long s0) {
   h->wca.resize(kFactorWindow);
   h->wma.resize(kFactorWindow);
   for (int k = 0; k < kFactorWindow; ++k)
-    step_args(h, s0 + k, h->cur_is_A == ((k & 1) == 0), h->wca[k], h->wma[k]);
+    step_args(h, s0 + k, h->wca[k], h->wma[k]);
   if (h->pin_pending) HIP_TRY(h, hipEventSynchronize(h->pin_ev));
   char* dev = h->sb + h->L.argtab.off;
   const size_t cb = (size_t)kFactorWindow * sizeof(CollideArgs), mb = (size_t)kFactorWindow * sizeof(MarkerArgs);
@@ -796,20 +801,115 @@ bool has_zou_he(const ibmlbm_config& c) {
   return c.bc[0] >= IBMLBM_BC_ZH_VELOCITY || c.bc[1] >= IBMLBM_BC_ZH_VELOCITY;
 }
 
+bool check_step(const ibmlbm_config& c, long long s) {
+  return c.check_interval > 0 && (s + 1) % c.check_interval == 0;
+}
+
+// Whether the solve's shape and storage have a two-step pass (pair.hip): FP32
+// (the 16-bit update there is bound by its arithmetic, not by the bytes a
+// second step saves: periodic 512x384x384 FP16 0.94 ms a step against 0.98,
+// with foils 1.15 against 1.06), a span of 4 layers or more (support rows that
+// wrap onto one another have no halo rows) and rows of lanes that address the
+// n_y slabs of their z with 31-bit offsets.
+bool pair_shape(ibmlbm_t h) {
+  const ibmlbm_config& c = h->cfg;
+  return c.storage == IBMLBM_FP32 && c.nz >= 4 && (long long)c.ny * kQ * h->L.px * h->L.es < (1LL << 31);
+}
+
+// Planes along y per block (`planes[j]`) of the solves of a call that take
+// their steps in pairs, 0 for those that do not: all that have such a pass, or
+// none, by what the two ways are expected to cost.
+//  one by one  8 us of launch and ramp for two steps, and the lattice read and
+//              written twice at 5.95 TB/s: 51.1 us per 10^6 cells;
+//  in pairs    3.8 us per plane of a block's march where blocks do not wait on
+//              memory, of which each compute unit holds one block at a time, a
+//              block of L planes taking L + 2; 11.7 us per 10^6 cells that
+//              memory adds; 5 us of launch; with foils 15 us for the cells
+//              around them and 2 us per plane of a block that meets a foil.
+// L is the one with the least march (the longer of two alike).
+// Measured (us for two steps, without markers, one by one / in pairs): 64^3
+// 24 / 28, 96x80x80 43 / 33, 128x96x96 69 / 46, 160x128x128 142 / 115,
+// 256x192x192 483 / 327, 512x384x384 3926 / 2455; with foils and their markers
+// 128x96x96 113 / 117, 160x128x128 191 / 226, 256x192x192 552 / 424.
+void plan_pairs(ibmlbm_t* hs, int n, int steps, int* planes) {
+  static const int lens[] = {64, 56, 48, 40, 32, 28, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4};
+  for (int j = 0; j < n; ++j) planes[j] = 0;
+  if (steps < 2) return;
+  double cells = 0.0, best = 1e300;
+  bool foils = false;
+  int best_len = 0, march = 0;
+  for (int j = 0; j < n; ++j)
+    if (pair_shape(hs[j])) {
+      cells += (double)hs[j]->L.N;
+      foils = foils || hs[j]->nw > 0;
+    }
+  if (cells == 0.0) return;
+  // ny planes in blocks of at most len, as even as they go
+  auto even = [](int ny, int len) {
+    const int blocks = (ny + len - 1) / len;
+    return (ny + blocks - 1) / blocks;
+  };
+  for (int len : lens) {
+    long long blocks = 0;
+    int longest = 0;
+    for (int j = 0; j < n; ++j)
+      if (pair_shape(hs[j])) {
+        const int l = even(hs[j]->cfg.ny, len);
+        blocks += pair_blocks(hs[j]->geo, l);
+        longest = std::max(longest, l);
+      }
+    // blocks a compute unit takes one after the other: whole rounds of few,
+    // half a block of slack at the end of many
+    const double rounds = blocks <= 4 * kCUs ? std::ceil((double)blocks / kCUs) : (double)blocks / kCUs + 0.5;
+    const double cost = rounds * (longest + 2);
+    if (cost < best) best = cost, best_len = len, march = longest;
+  }
+  const double extra = foils ? 15.0 + 2.0 * std::min(march, 30) : 0.0;
+  if (5.0 + 3.8 * best + extra + 11.7e-6 * cells > 8.0 + 51.1e-6 * cells) return;
+  for (int j = 0; j < n; ++j)
+    if (pair_shape(hs[j])) planes[j] = even(hs[j]->cfg.ny, best_len);
+}
+
+// Whether steps s and s + 1 of h, both in its current window, can be taken in
+// one pass: neither is a check step (those sum the density of every cell of
+// the state between), and the marker kernels of step s + 1 find all they read
+// in the cells that step s is given first (near_region, which does not wrap).
+bool pair_ok(ibmlbm_t h, long long s) {
+  const ibmlbm_config& c = h->cfg;
+  const int slot = (int)(s - h->win_t0);
+  if (slot + 1 >= kFactorWindow || check_step(c, s) || check_step(c, s + 1)) return false;
+  for (int k = 0; k < h->nw; ++k)
+    for (int i = slot; i <= slot + 1; ++i) {
+      const FoilBox& b = h->wca[i].box[k];
+      if (b.x0 < 1 || b.x0 + b.w + 1 > c.nx) return false;
+      if (h->geo.yper && (b.y0 < 1 || b.y0 + b.h + 1 > c.ny)) return false;
+    }
+  return true;
+}
+
 // `steps` time steps of every handle in hs (one stream).  Each stage of a
 // step is one grouped launch over the handles that share its kernel
 // instantiation, so small solves fill the device together and each solve
-// runs the same code as alone.
+// runs the same code as alone.  A solve that can takes its steps in pairs:
+// markers of s, step s of the cells around the foils, markers of s + 1, then
+// both steps of the whole lattice in one pass.
 int run_steps(ibmlbm_t* hs, int n, int steps) {
   hipStream_t st = hs[0]->stream;
   const bool timed = n == 1;
+  enum Mode : char { SINGLE, FIRST, SECOND };
+  Mode mode[kMaxGroup];
+  int planes[kMaxGroup];
+  for (int j = 0; j < n; ++j) mode[j] = SINGLE;
+  plan_pairs(hs, n, steps, planes);
   std::vector<const MarkerArgs*> mh;
   std::vector<const CollideArgs*> chh;
-  std::vector<const void*> dv;
+  std::vector<const void*> dv, src;
+  std::vector<void*> dst;
+  std::vector<int> ylen;
+  auto clear = [&] { mh.clear(); chh.clear(); dv.clear(); src.clear(); dst.clear(); ylen.clear(); };
   for (int k = 0; k < steps; ++k) {
     // windows that start at this step; their factor launch
-    mh.clear();
-    dv.clear();
+    clear();
     for (int j = 0; j < n; ++j) {
       ibmlbm_t h = hs[j];
       const long long s = h->step;
@@ -821,9 +921,11 @@ int run_steps(ibmlbm_t* hs, int n, int steps) {
           dv.push_back(dev_ma(h, 0));
         }
       }
+      mode[j] = mode[j] == FIRST ? SECOND : (planes[j] > 0 && k + 1 < steps && pair_ok(h, s) ? FIRST : SINGLE);
     }
     bool any_ibm = false;
     for (int j = 0; j < n; ++j) any_ibm = any_ibm || hs[j]->nw > 0;
+    if (timed) time_step(hs[0], mode[0] == FIRST, mode[0] == SECOND);
     if (timed && any_ibm) {
       int rc = record_event(hs[0], st, 1, true);
       if (rc) return rc;
@@ -832,51 +934,76 @@ int run_steps(ibmlbm_t* hs, int n, int steps) {
       hipError_t e = launch_factor(mh.data(), dv.data(), (int)mh.size(), kFactorWindow, st);
       if (e != hipSuccess) return fail(hs[0], IBMLBM_EDEVICE, "factor launch: %s", hipGetErrorString(e));
     }
-    // marker kernels, grouped by storage
+    // marker kernels, grouped by storage; the second step of a pair starts
+    // from the cells around the foils that its first step wrote ahead
     for (int sto = 0; sto < 3; ++sto) {
-      mh.clear();
-      dv.clear();
+      clear();
+      unsigned long long alt = 0;
       for (int j = 0; j < n; ++j) {
         ibmlbm_t h = hs[j];
         if (h->nw == 0 || h->cfg.storage != sto) continue;
         const int slot = (int)(h->step - h->win_t0);
+        if (mode[j] == SECOND) alt |= 1ULL << mh.size();
         mh.push_back(&h->wma[slot]);
         dv.push_back(dev_ma(h, slot));
+        src.push_back(mode[j] == SECOND ? next_state(h) : cur_state(h));
       }
       if (mh.empty()) continue;
-      hipError_t e = launch_markers(sto, mh.data(), dv.data(), (int)mh.size(), st);
+      hipError_t e = launch_markers(sto, mh.data(), dv.data(), src.data(), alt, (int)mh.size(), st);
       if (e != hipSuccess) return fail(hs[0], IBMLBM_EDEVICE, "marker launch: %s", hipGetErrorString(e));
+    }
+    // the solves of mode m that one instantiation of its lattice kernel takes
+    // (storage, Zou-He faces, foils, body force, check step); the arguments
+    // of a pair are those of its first step
+    auto pick = [&](Mode m, int key) {
+      clear();
+      const int sto = key >> 4;
+      const bool zh = key & 8, ibm = key & 4, force = key & 2, check = key & 1;
+      for (int j = 0; j < n; ++j) {
+        ibmlbm_t h = hs[j];
+        const ibmlbm_config& c = h->cfg;
+        if (mode[j] != m || c.storage != sto || (h->nw > 0) != ibm || has_force(c) != force ||
+            check_step(c, h->step) != check || has_zou_he(c) != zh)
+          continue;
+        const int slot = (int)(h->step - h->win_t0) - (m == SECOND);
+        chh.push_back(&h->wca[slot]);
+        dv.push_back(dev_ca(h, slot));
+        src.push_back(cur_state(h));
+        dst.push_back(next_state(h));
+        ylen.push_back(planes[j]);
+      }
+      return !chh.empty();
+    };
+    for (int key = 0; key < 48; ++key) {
+      if (!(key & 4) || (key >> 4) != IBMLBM_FP32 || !pick(FIRST, key)) continue;
+      hipError_t e = launch_near(key & 2, key & 8, chh.data(), dv.data(), src.data(), dst.data(),
+                                 (int)chh.size(), st);
+      if (e != hipSuccess) return fail(hs[0], IBMLBM_EDEVICE, "near launch: %s", hipGetErrorString(e));
     }
     if (timed && any_ibm) {
       int rc = record_event(hs[0], st, 1, false);
       if (rc) return rc;
     }
-    // collide, grouped by (storage, foils, body force, check step)
-    if (timed) {
-      int rc = record_event(hs[0], st, 0, true, (double)hs[0]->L.N);
+    const bool lattice = mode[0] != FIRST;
+    if (timed && lattice) {
+      int rc = record_event(hs[0], st, 0, true, (double)hs[0]->L.N * (mode[0] == SECOND ? 2 : 1));
       if (rc) return rc;
     }
     for (int key = 0; key < 48; ++key) {
       const int sto = key >> 4;
       const bool zh = key & 8, ibm = key & 4, force = key & 2, check = key & 1;
-      chh.clear();
-      dv.clear();
-      for (int j = 0; j < n; ++j) {
-        ibmlbm_t h = hs[j];
-        const ibmlbm_config& c = h->cfg;
-        const bool ck = c.check_interval > 0 && ((h->step + 1) % c.check_interval == 0);
-        if (c.storage != sto || (h->nw > 0) != ibm || has_force(c) != force || ck != check ||
-            has_zou_he(c) != zh)
-          continue;
-        const int slot = (int)(h->step - h->win_t0);
-        chh.push_back(&h->wca[slot]);
-        dv.push_back(dev_ca(h, slot));
+      if (pick(SINGLE, key)) {
+        hipError_t e = launch_collide(sto, ibm, force, check, zh, chh.data(), dv.data(), src.data(), dst.data(),
+                                      (int)chh.size(), st);
+        if (e != hipSuccess) return fail(hs[0], IBMLBM_EDEVICE, "collide launch: %s", hipGetErrorString(e));
       }
-      if (chh.empty()) continue;
-      hipError_t e = launch_collide(sto, ibm, force, check, zh, chh.data(), dv.data(), (int)chh.size(), st);
-      if (e != hipSuccess) return fail(hs[0], IBMLBM_EDEVICE, "collide launch: %s", hipGetErrorString(e));
+      if (sto == IBMLBM_FP32 && !check && pick(SECOND, key)) {
+        hipError_t e = launch_pair(ibm, force, zh, chh.data(), dv.data(), src.data(), dst.data(), ylen.data(),
+                                   (int)chh.size(), st);
+        if (e != hipSuccess) return fail(hs[0], IBMLBM_EDEVICE, "pair launch: %s", hipGetErrorString(e));
+      }
     }
-    if (timed) {
+    if (timed && lattice) {
       int rc = record_event(hs[0], st, 0, false);
       if (rc) return rc;
     }
@@ -884,11 +1011,11 @@ int run_steps(ibmlbm_t* hs, int n, int steps) {
       ibmlbm_t h = hs[j];
       const ibmlbm_config& c = h->cfg;
       const long long s = h->step;
-      if (c.check_interval > 0 && ((s + 1) % c.check_interval == 0))
+      if (check_step(c, s))
         HIP_TRY(h, launch_mass_reduce(at<double>(h, h->L.mass_part), h->L.nblocks,
                                       (double)h->L.N,
                                       reinterpret_cast<double*>(h->sb + h->L.diag.off), s + 1, st));
-      h->cur_is_A = !h->cur_is_A;
+      if (mode[j] != FIRST) h->cur_is_A = !h->cur_is_A;
       h->step = s + 1;
       if (h->nw > 0) h->markers_valid = true;
     }

@@ -14,193 +14,27 @@
 // Distributions are stored as deviations from the lattice weights,
 // f~_i = f_i - w_i, so FP32 (and 16-bit) storage keeps the small velocity
 // signal out of the rounding of the O(w_i) rest value.
-#include "lattice_dev.h"
+#include "update_dev.h"
 
 namespace ibmk {
 
 // ---------------------------------------------------------------- collide --
 
-// True if (x, y) lies in the node box of foil w.
-__device__ __forceinline__ bool in_box(const FoilBox& b, int x, int y) {
-  return y >= b.y0 && y < b.y0 + b.h && x >= b.x0 && x < b.x0 + b.w;
-}
-
-// du(x) of the IBM correction (Eq. 15): the sum over foils and the 4 span
-// layers within reach of the layer images written by the spread kernel.
-// Returns whether the cell is a support node of a foil's markers (elsewhere
-// the correction is exactly zero and the images are not read).
-__device__ __forceinline__ bool correction(const CollideArgs& a, int x, int y, int z, float& dux,
-                                           float& duy, float& duz) {
-  const Geo& g = a.g;
-  dux = duy = duz = 0.f;
-  bool hit = false;
-  for (int w = 0; w < a.nw; ++w) {
-    const FoilBox& b = a.box[w];
-    if (y < b.y0 || y >= b.y0 + b.h) continue;         // wave-uniform: most rows miss
-    if (!in_box(b, x, y)) continue;
-    const int lx = x - b.x0, ly = y - b.y0;
-    if (!((b.bits[ly * b.words + (lx >> 5)] >> (lx & 31)) & 1u)) continue;   // zero there
-    hit = true;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      int s = z - 2 + k;
-      s = s < 0 ? s + g.nz : (s >= g.nz ? s - g.nz : s);
-      s = s < 0 ? s + g.nz : s;                        // a span of one layer wraps twice
-      const float4 v = b.corr[((long long)s * b.side + ly) * b.side + lx];
-      dux += a.wz[k] * v.x;
-      duy += a.wz[k] * v.y;
-      duz += a.wz[k] * v.z;
-    }
-  }
-  return hit;
-}
-
-// One cell update: pull-streaming, the Zou-He rebuild at the x faces (ZH:
-// the solve has Zou-He faces), moments, optional IBM velocity
-// correction and Guo forcing, BGK relaxation, streaming store of the
-// post-collision values and, at x = 0 / nx-1, the ghost layer of the next
+// One cell update: pull-streaming, the update of the cell, streaming store of
+// the post-collision values and, at x = 0 / nx-1, the ghost layer of the next
 // state.  Returns the density deviation of the pre-collision state.
-// Everything is computed in stored units
-// (kS f~): the moments, the equilibrium (Eq. 4, with rho scaled) and the
-// Guo term (Eq. 8, with F scaled) are linear in the distributions, and kS is
-// a power of two, so the result is the same as in units of f~.
-template <class St, bool IBM, bool FORCE, bool ZH = false>
+template <class St, bool IBM, bool FORCE, bool ZH>
 __device__ __forceinline__ float collide_cell(const CollideArgs& a, const typename St::T* __restrict__ S,
                                               typename St::T* __restrict__ D, int x, int y, int z) {
-  using T = typename St::T;
-  constexpr float kS = St::kS, kInv = St::kInv;
-  const Geo& g = a.g;
   float f[kQ];
-  // wave-uniform row: the scalar-base pull where no y or z wall reflects
-  // into the row
-  if (pull_rows_inside(g, y, z))
-    pull19_rows<St>(S, g, x, y, z, f);
-  else
-    pull19<St, true>(S, g, x, y, z, f);
+  pull_row<St>(S, a.g, x, y, z, f);
   // IBM correction: with Zou-He faces it is fetched while the pull is in
   // flight (measured faster there), else after the moments
-  float dux = 0.f, duy = 0.f, duz = 0.f;
-  bool hit = false;
-  if (IBM && ZH) hit = correction(a, x, y, z, dux, duy, duz);
-  if constexpr (ZH) {
-    // Zou-He x faces: rebuild the entering populations at the face lanes
-    // (the rule of zou_he, each face's branch on its own so the rest of
-    // the row keeps f in registers)
-    if ((g.yper || (y > 0 && y < g.ny - 1)) && (g.zper || (z > 0 && z < g.nz - 1))) {
-      if (x == 0 && g.bclo >= BC_ZH_VELOCITY) zou_he_face<St, true, 1>(a.p, g.bclo, f);
-      if (x == g.nx - 1 && x != 0 && g.bchi >= BC_ZH_VELOCITY) zou_he_face<St, true, -1>(a.p, g.bchi, f);
-    }
-  }
-  float dr, jx, jy, jz;                            // kS drho, kS j
-  moments19(f, dr, jx, jy, jz);
-  const float drho = dr * kInv;
-  const float rho = 1.0f + drho;
-  const float srho = kS * rho;
-  const float inv = 1.0f / srho;
-  float Fx = 0.f, Fy = 0.f, Fz = 0.f;                // kS F
-  if (FORCE) {
-    Fx = kS * a.p.fb[0]; Fy = kS * a.p.fb[1]; Fz = kS * a.p.fb[2];
-    jx += 0.5f * Fx; jy += 0.5f * Fy; jz += 0.5f * Fz;
-  }
-  float ux = jx * inv, uy = jy * inv, uz = jz * inv;
-  bool forced = FORCE;
-  if (IBM) {
-    if (!ZH) hit = correction(a, x, y, z, dux, duy, duz);
-    if (hit) {
-      ux += dux; uy += duy; uz += duz;                 // Eq. 16
-      Fx += 2.0f * srho * dux;                         // Eq. 11 / Eq. 26
-      Fy += 2.0f * srho * duy;
-      Fz += 2.0f * srho * duz;
-      forced = true;
-    }
-  }
-  const float usq = ux * ux + uy * uy + uz * uz;
-  const float om = a.p.omega;
-  // Equilibrium (Eq. 4) by opposite pairs: with cu_opp = -cu, the even part
-  // w (drho + rho (4.5 cu^2 - 1.5 u^2)) is shared and the odd part 3 w rho cu
-  // changes sign, so each pair costs one evaluation
-  const float c15 = 1.5f * usq;
-  const float k1[2] = {wq(1) * srho, wq(7) * srho}, k3[2] = {3.0f * wq(1) * srho, 3.0f * wq(7) * srho},
-              kd[2] = {wq(1) * dr, wq(7) * dr};
-  float o[kQ];
-  o[0] = f[0] - om * (f[0] - (wq(0) * dr - wq(0) * srho * c15));
-#pragma unroll
-  for (int i = 1; i < kQ; ++i) {
-    if (oppq(i) < i) continue;
-    const int c = i < 7 ? 0 : 1;                       // axis or diagonal weight
-    const float cu = cdot(i, ux, uy, uz);
-    const float A = k1[c] * (4.5f * cu * cu - c15) + kd[c];
-    const float B = k3[c] * cu;
-    const float fp = A + B, fm = A - B;                // feq of i and of opp(i)
-    o[i] = f[i] - om * (f[i] - fp);
-    o[oppq(i)] = f[oppq(i)] - om * (f[oppq(i)] - fm);
-  }
-  if (forced) {
-    const float k = a.p.guo_k;
-    const float uF = ux * Fx + uy * Fy + uz * Fz;
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      const float cu = cdot(i, ux, uy, uz);
-      const float cF = cdot(i, Fx, Fy, Fz);
-      o[i] += k * wq(i) * (3.0f * (cF - uF) + 9.0f * cu * cF);   // Eq. 8
-    }
-  }
-  T* own = D + rowbase(g, y, z);
-  if constexpr (sizeof(T) == 2) {
-    // 16-bit storage: one buffer descriptor over the cell row's 19
-    // population rows, so each store takes its row as a scalar offset and
-    // the lane's x as the vector offset, with no per-store address
-    // arithmetic (FP32 measured faster with plain stores)
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(own, 0, (int)(kQ * g.ps * (long long)sizeof(T)), kRawBufferWord3);
-    const int bo = x * (int)sizeof(T);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) St::stb(rs, bo, (int)(i * g.ps * (long long)sizeof(T)), o[i]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) St::stnr(own + (long long)i * g.ps + x, o[i]);
-  }
-  if (x == 0 || x == g.nx - 1) {
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) o[i] *= kInv;
-    write_ghosts<St>(D, g, a.p, x, y, z, o);
-  }
+  Correction c;
+  if (IBM && ZH) c = correction(a.g, a, x, y, z);
+  const float drho = update_cell<St, IBM, FORCE, ZH, ZH>(a.g, a.p, a, x, y, z, f, c);
+  store_cell<St>(D, a.g, a.p, x, y, z, f);
   return drho;
-}
-
-// Block 0 of a collide launch after the marker kernels: per foil, the sum
-// over span layers of the layer forces and moments in a fixed order, the
-// coefficients (Sec. 3.6-3.7: lift is the lateral component, counted outward
-// for a mirrored pair; thrust is -F_x; drag = -thrust) and the history row.
-__device__ void reduce_forces(const CollideArgs& a) {
-  __shared__ double red[4][kBlockX * kBlockRows];
-  const int t = threadIdx.y * kBlockX + threadIdx.x, nt = kBlockX * kBlockRows;
-  for (int w = 0; w < a.nw; ++w) {
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    const double* fp = a.fpart + 4 * (size_t)w * a.g.nz;
-    for (int l = t; l < a.g.nz; l += nt)
-      for (int k = 0; k < 4; ++k) v[k] += fp[4 * l + k];
-    for (int k = 0; k < 4; ++k) red[k][t] = v[k];
-    __syncthreads();
-    for (int h = nt / 2; h > 0; h >>= 1) {
-      if (t < h)
-        for (int k = 0; k < 4; ++k) red[k][t] += red[k][t + h];
-      __syncthreads();
-    }
-    if (t == 0) {
-      const double F0 = red[0][0], F1 = red[1][0], F2 = red[2][0], F3 = red[3][0];
-      double* h = a.hist + ((size_t)a.hist_row * a.nw + w) * 8;
-      h[0] = F0;
-      h[1] = F1;
-      h[2] = F2;
-      h[3] = F3;
-      h[4] = -a.sense[w] * F1 / a.qS;
-      h[5] = -F0 / a.qS;
-      h[6] = F0 / a.qS;
-      h[7] = F3 / (a.qS * a.chord[w]);
-    }
-    __syncthreads();
-  }
 }
 
 // Every cell, one row per wave, 64 cells along x per wave, 4 waves per block.
@@ -315,15 +149,15 @@ static hipError_t launch_collide_s(bool ibm, bool force, bool check, bool zh, co
 }
 
 hipError_t launch_collide(int storage, bool ibm, bool force, bool check, bool zh,
-                          const CollideArgs* const* host, const void* const* dev, int n,
-                          hipStream_t s) {
+                          const CollideArgs* const* host, const void* const* dev, const void* const* src,
+                          void* const* dst, int n, hipStream_t s) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   CollideGroup g;
   int blocks[kMaxGroup];
   for (int k = 0; k < n; ++k) {
     blocks[k] = host[k]->nblocks;
-    g.src[k] = host[k]->src;
-    g.dst[k] = host[k]->dst;
+    g.src[k] = src[k];
+    g.dst[k] = dst[k];
   }
   const int total = group_fill(g.g, dev, blocks, n);
   if (total == 0) return hipSuccess;

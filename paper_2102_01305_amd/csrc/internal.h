@@ -14,6 +14,10 @@ constexpr int kMaxWings = 8;
 constexpr int kMaxPerim = 128;     // perimeter markers per foil (LDS of the inversion)
 constexpr int kBlockX = 64;        // collide block: 64 cells along x ...
 constexpr int kBlockRows = 4;      // ... times 4 rows, one row per wave
+constexpr int kPairRows = 12;       // two-step pass: rows along z of a block's column ...
+constexpr int kPairThreads = (kPairRows + 3) * 64;   // ... a wave each, two beside them, one for the x sides
+constexpr int kPairPlanes = 64;     // most planes along y of such a column
+constexpr int kCUs = 256;           // compute units of the device
 constexpr int kFactorWindow = 64;  // steps whose perimeter factors (and launch arguments) are made at once
 constexpr int kMaxGroup = 64;      // solves in one grouped launch
 
@@ -69,8 +73,6 @@ struct FoilBox {
 struct CollideArgs {
   Geo g;
   Phys p;
-  const void* src;
-  void* dst;
   int nw;                    // foils whose correction the kernel applies
   FoilBox box[kMaxWings];
   float wz[4];               // span weights delta(1.5), delta(0.5), delta(0.5), delta(1.5)
@@ -89,6 +91,16 @@ struct CollideArgs {
   double sense[kMaxWings], chord[kMaxWings];
 };
 
+// Cells around a foil that step s + 1's marker kernels pull from: its node box
+// of that step, which reaches past every neighbour of a support node by a
+// spare cell, and one cell more; clipped to the box.
+__host__ __device__ inline void near_region(const FoilBox& b, const Geo& g, int& x0, int& y0, int& w, int& h) {
+  x0 = b.x0 > 0 ? b.x0 - 1 : 0;
+  y0 = b.y0 > 0 ? b.y0 - 1 : 0;
+  w = (b.x0 + b.w + 1 < g.nx ? b.x0 + b.w + 1 : g.nx) - x0;
+  h = (b.y0 + b.h + 1 < g.ny ? b.y0 + b.h + 1 : g.ny) - y0;
+}
+
 // A grouped launch: the blocks of solve k are start[k] .. start[k+1]-1 and
 // read that solve's arguments from device memory at args[k].  One solve is a
 // group of one, so a solve runs the same code alone and in a group.
@@ -98,12 +110,24 @@ struct Group {
   const void* args[kMaxGroup];
 };
 
-// launch wrappers of collide.hip (the marker kernels' are in marker_args.h);
-// all enqueue on `s` and return hipError_t.  `host[k]` is the host copy of the arguments that `dev[k]`
-// holds on the device (used for grid and LDS sizing only).
+// launch wrappers of collide.hip and pair.hip (the marker kernels' are in
+// marker_args.h); all enqueue on `s` and return hipError_t.  `host[k]` is the
+// host copy of the arguments that `dev[k]` holds on the device (used for grid
+// and LDS sizing only); `src[k]`, `dst[k]` are the solve's states.
 hipError_t launch_collide(int storage, bool ibm, bool force, bool check, bool zh,
-                          const CollideArgs* const* host, const void* const* dev, int n,
-                          hipStream_t s);
+                          const CollideArgs* const* host, const void* const* dev, const void* const* src,
+                          void* const* dst, int n, hipStream_t s);
+// Two steps of FP32 states in one pass: dev[k] is the first step's arguments, followed by
+// the second's; ylen[k] planes per block.
+hipError_t launch_pair(bool ibm, bool force, bool zh, const CollideArgs* const* host,
+                       const void* const* dev, const void* const* src, void* const* dst, const int* ylen,
+                       int n, hipStream_t s);
+// The first of two steps on the cells that the marker kernels of the second
+// read (arguments as launch_pair), and that step's force reduction.
+hipError_t launch_near(bool force, bool zh, const CollideArgs* const* host, const void* const* dev,
+                       const void* const* src, void* const* dst, int n, hipStream_t s);
+// Blocks of a solve's pair pass with columns of `ylen` planes.
+int pair_blocks(const Geo& g, int ylen);
 hipError_t launch_ghost(int storage, const Geo& g, const Phys& p, void* buf, hipStream_t s);
 hipError_t launch_init_eq(int storage, const Geo& g, const double* rho, const double* u,
                           void* dst, hipStream_t s);

@@ -38,8 +38,9 @@ __host__ __device__ constexpr double wqd(int i) {
 // ld()/st() take and give f~ itself; ldr()/stnr() the stored value, which is
 // kS f~ (kS = 2^12 for FP16, else 1), for the collide kernel, which works
 // in those units throughout.  stn/stnr are streaming (non-temporal) stores
-// for data the current kernel will not read again; stb is stnr through a
-// buffer descriptor (byte offsets: vo per lane, so from a scalar register).
+// for data the current kernel will not read again; stb is stnr (and ldb, for
+// FP32, ldr) through a buffer descriptor (byte offsets: vo per lane, so from a
+// scalar register).
 constexpr int kRawBufferWord3 = 0x00020000;   // untyped (raw) buffer, 32-bit data format
 constexpr int kStreamAux = 2;                 // non-temporal
 struct StF32 {
@@ -50,6 +51,9 @@ struct StF32 {
   __device__ static void stn(T* p, float v) { __builtin_nontemporal_store(v, p); }
   __device__ static float ldr(const T* p) { return *p; }
   __device__ static void stnr(T* p, float v) { __builtin_nontemporal_store(v, p); }
+  __device__ static float ldb(__amdgpu_buffer_rsrc_t r, int vo, int so) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+  }
   __device__ static void stb(__amdgpu_buffer_rsrc_t r, int vo, int so, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, vo, so, kStreamAux);
   }
@@ -348,6 +352,21 @@ __device__ __forceinline__ float feq_dev_strict(int i, float drho, float rho, fl
   return wq(i) * (drho + rho * (3.0f * cu + 4.5f * cu * cu - 1.5f * usq));
 }
 
+// Density and velocity of the ghost layer of an open x face (inlet or
+// outlet) beside a boundary cell of density rho and momentum j.
+__device__ __forceinline__ void open_face(const Phys& p, int kind, float rho, float jx, float jy, float jz,
+                                          float& rg, float& ux, float& uy, float& uz) {
+#pragma clang fp contract(off)
+  if (kind == BC_VELOCITY || kind == BC_ZH_VELOCITY) {
+    rg = rho;
+    ux = p.u_in[0]; uy = p.u_in[1]; uz = p.u_in[2];
+  } else {  // BC_PRESSURE, BC_ZH_PRESSURE
+    rg = p.rho_out;
+    const float inv = 1.0f / rho;
+    ux = jx * inv; uy = jy * inv; uz = jz * inv;
+  }
+}
+
 // Ghost records of the state being written, from the post-collision values
 // `o` of a boundary cell (x == 0 or x == nx-1).  The ghost at (-1, y', z')
 // for population i (c_x = +1) is read only by cell (0, y'+c_y, z'+c_z); the
@@ -391,14 +410,7 @@ __device__ void write_ghosts(typename St::T* __restrict__ D, const Geo& g, const
       continue;
     }
     float rg, ux, uy, uz;
-    if (kind == BC_VELOCITY || kind == BC_ZH_VELOCITY) {
-      rg = rho;
-      ux = p.u_in[0]; uy = p.u_in[1]; uz = p.u_in[2];
-    } else {  // BC_PRESSURE, BC_ZH_PRESSURE
-      rg = p.rho_out;
-      const float inv = 1.0f / rho;
-      ux = jx * inv; uy = jy * inv; uz = jz * inv;
-    }
+    open_face(p, kind, rho, jx, jy, jz, rg, ux, uy, uz);
     const float usq = ux * ux + uy * uy + uz * uz;
 #pragma unroll
     for (int i = 0; i < kQ; ++i)

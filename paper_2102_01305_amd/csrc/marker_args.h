@@ -36,7 +36,6 @@ struct MarkerArgs {
   double wz[4];              // span weights of a node at offsets -1.5, -0.5, 0.5, 1.5
   double t;
   double pose[kMaxWings][6]; // per foil at t: theta, dtheta/dt, pivot x, y, pivot velocity x, y
-  const void* src;           // current state (post-collision of the previous step)
   const double* ref;
   const double* G;
   double* Minv;              // [window slot][sum np^2] perimeter inverses
@@ -66,8 +65,10 @@ struct MarkerArgs {
 // device (used for grid and LDS sizing only).
 hipError_t launch_factor(const MarkerArgs* const* host, const void* const* dev, int n, int count,
                          hipStream_t s);
-hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void* const* dev, int n,
-                          hipStream_t s);
+// `src[k]`: the state the step starts from (post-collision of the previous
+// step); solves with bit k of `alt` set get the spread image in `band`.
+hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void* const* dev,
+                          const void* const* src, unsigned long long alt, int n, hipStream_t s);
 // LDS bytes of the per-marker interpolation and span-solve block for a span
 // of ns layers, against the device's kMaxLds per block.
 size_t marker_span_lds(int ns);

@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(256) k_factor(Group gr) {
 // waves past the list's length (the host sizes the grid from a bound) end at
 // once.
 template <class St>
-__device__ __forceinline__ void band_block(const MarkerArgs& __restrict__ a, int lb) {
+__device__ __forceinline__ void band_block(const MarkerArgs& __restrict__ a, int lb, const void* src) {
   using T = typename St::T;
   int R = __builtin_amdgcn_readfirstlane((int)(lb * 4 + (threadIdx.x >> 6)));
   const int lane = threadIdx.x & 63;
@@ -258,7 +258,7 @@ __device__ __forceinline__ void band_block(const MarkerArgs& __restrict__ a, int
   if (e >= (int)cnt) return;
   const int lx = (int)(cell & 0xffffu), ly = (int)(cell >> 16);
   float f[kQ];
-  pull19<St>(static_cast<const T*>(a.src), a.g, w.x0 + lx, w.y0 + ly, z, f);
+  pull19<St>(static_cast<const T*>(src), a.g, w.x0 + lx, w.y0 + ly, z, f);
   zou_he<St, false>(a.g, a.p, w.x0 + lx, w.y0 + ly, z, f);
   float drho, jx, jy, jz;
   moments19(f, drho, jx, jy, jz);
@@ -267,11 +267,16 @@ __device__ __forceinline__ void band_block(const MarkerArgs& __restrict__ a, int
       make_float4(rho, (jx + 0.5f * a.p.fb[0]) / rho, (jy + 0.5f * a.p.fb[1]) / rho, (jz + 0.5f * a.p.fb[2]) / rho);
 }
 
+struct BandGroup {
+  Group g;
+  const void* src[kMaxGroup];
+};
+
 template <class St>
-__global__ void __launch_bounds__(256) k_band(Group gr) {
+__global__ void __launch_bounds__(256) k_band(BandGroup gr) {
   int lb;
-  const MarkerArgs* a = static_cast<const MarkerArgs*>(group_find(gr, lb));
-  band_block<St>(*a, lb);
+  const int k = group_index(gr.g, lb);
+  band_block<St>(*static_cast<const MarkerArgs*>(gr.g.args[k]), lb, gr.src[k]);
 }
 
 __device__ __forceinline__ int find_layer_block(const MarkerArgs& a, int blk, int& wi) {
@@ -474,7 +479,7 @@ __global__ void __launch_bounds__(512) k_interp_span(Group gr) {
 // images, each added by one wave over the markers p = copy (mod copies) in
 // order, then summed copy by copy, so the sums are the same on every run.  The perimeter inverse is read from L2
 // (measured faster than staging it in LDS, also where it fits).
-__device__ __forceinline__ void layer_block(const MarkerArgs& __restrict__ a, int lb) {
+__device__ __forceinline__ void layer_block(const MarkerArgs& __restrict__ a, int lb, bool alt) {
   extern __shared__ double lds[];
   __shared__ double red[4][256];
   int wi;
@@ -549,7 +554,9 @@ __device__ __forceinline__ void layer_block(const MarkerArgs& __restrict__ a, in
   if (threadIdx.x < 4) a.fpart[4 * ((size_t)w.layer_off + s) + threadIdx.x] = red[threadIdx.x][0];
   // only the support nodes of this step are written: the collide kernel
   // reads the image nowhere else (its support bitmap)
-  float4* out = w.corr + (size_t)s * w.side * w.side;
+  // (in the second step of a pair the first step's image is still needed, and
+  // the band moments are not any more: their image takes it)
+  float4* out = (alt ? w.band : w.corr) + (size_t)s * w.side * w.side;
   const auto* list = gmem(a.sup + (size_t)a.slot * a.sup_step + w.sup_off);
   const int cnt = (int)list[0];
   for (int e = threadIdx.x; e < cnt; e += blockDim.x) {
@@ -563,10 +570,10 @@ __device__ __forceinline__ void layer_block(const MarkerArgs& __restrict__ a, in
   }
 }
 
-__global__ void __launch_bounds__(256) k_layer(Group gr) {
+__global__ void __launch_bounds__(256) k_layer(Group gr, unsigned long long alt) {
   int lb;
-  const MarkerArgs* a = static_cast<const MarkerArgs*>(group_find(gr, lb));
-  layer_block(*a, lb);
+  const int k = group_index(gr, lb);
+  layer_block(*static_cast<const MarkerArgs*>(gr.args[k]), lb, (alt >> k) & 1);
 }
 
 size_t marker_span_lds(int ns) { return interp_span_lds(ns); }
@@ -610,8 +617,8 @@ hipError_t launch_factor(const MarkerArgs* const* host, const void* const* dev, 
   return hipGetLastError();
 }
 
-hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void* const* dev, int n,
-                          hipStream_t s) {
+hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void* const* dev,
+                          const void* const* src, unsigned long long alt, int n, hipStream_t s) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   int nb[kMaxGroup], nl[kMaxGroup], np[kMaxGroup];
   size_t lds_l = 0, lds_s = 0;
@@ -641,13 +648,15 @@ hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void
   hipError_t e = raise_lds(reinterpret_cast<const void*>(k_layer), lds_l);
   if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(k_interp_span), lds_s);
   if (e != hipSuccess) return e;
-  Group g;
+  BandGroup bg;
+  Group& g = bg.g;
+  for (int j = 0; j < n; ++j) bg.src[j] = src[j];
   int total = group_fill(g, dev, nb, n);
   if (total > 0) {
     switch (storage) {
-      case ST_F32: k_band<StF32><<<total, 256, 0, s>>>(g); break;
-      case ST_F16: k_band<StF16><<<total, 256, 0, s>>>(g); break;
-      default: k_band<StBF16><<<total, 256, 0, s>>>(g); break;
+      case ST_F32: k_band<StF32><<<total, 256, 0, s>>>(bg); break;
+      case ST_F16: k_band<StF16><<<total, 256, 0, s>>>(bg); break;
+      default: k_band<StBF16><<<total, 256, 0, s>>>(bg); break;
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -658,7 +667,7 @@ hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   total = group_fill(g, dev, nl, n);
-  k_layer<<<total, 256, lds_l, s>>>(g);
+  k_layer<<<total, 256, lds_l, s>>>(g, alt);
   return hipGetLastError();
 }
 
