@@ -825,19 +825,22 @@ bool pair_shape(ibmlbm_t h) {
 //              memory, of which each compute unit holds one block at a time, a
 //              block of L planes taking L + 2; 11.7 us per 10^6 cells that
 //              memory adds; 5 us of launch; with foils 15 us for the cells
-//              around them and 2 us per plane of a block that meets a foil.
+//              around them and 2 us per plane of a march that meets one, at
+//              most 40.
 // L is the one with the least march (the longer of two alike).
 // Measured (us for two steps, without markers, one by one / in pairs): 64^3
 // 24 / 28, 96x80x80 43 / 33, 128x96x96 69 / 46, 160x128x128 142 / 115,
 // 256x192x192 483 / 327, 512x384x384 3926 / 2455; with foils and their markers
-// 128x96x96 113 / 117, 160x128x128 191 / 226, 256x192x192 552 / 424.
+// 128x96x96 113 / 117, 160x128x128 191 / 226, 256x192x192 552 / 424; 6, 8 and
+// 16 solves of the sweep's four sizes together 389 / 406, 624 / 606, 1232 / 1123.
 void plan_pairs(ibmlbm_t* hs, int n, int steps, int* planes) {
   static const int lens[] = {64, 56, 48, 40, 32, 28, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4};
   for (int j = 0; j < n; ++j) planes[j] = 0;
   if (steps < 2) return;
   double cells = 0.0, best = 1e300;
   bool foils = false;
-  int best_len = 0, march = 0;
+  int best_len = 0;
+  double march = 0.0;
   for (int j = 0; j < n; ++j)
     if (pair_shape(hs[j])) {
       cells += (double)hs[j]->L.N;
@@ -862,9 +865,9 @@ void plan_pairs(ibmlbm_t* hs, int n, int steps, int* planes) {
     // half a block of slack at the end of many
     const double rounds = blocks <= 4 * kCUs ? std::ceil((double)blocks / kCUs) : (double)blocks / kCUs + 0.5;
     const double cost = rounds * (longest + 2);
-    if (cost < best) best = cost, best_len = len, march = longest;
+    if (cost < best) best = cost, best_len = len, march = rounds * longest;
   }
-  const double extra = foils ? 15.0 + 2.0 * std::min(march, 30) : 0.0;
+  const double extra = foils ? 15.0 + 2.0 * std::min(march, 40.0) : 0.0;
   if (5.0 + 3.8 * best + extra + 11.7e-6 * cells > 8.0 + 51.1e-6 * cells) return;
   for (int j = 0; j < n; ++j)
     if (pair_shape(hs[j])) planes[j] = even(hs[j]->cfg.ny, best_len);
