@@ -45,7 +45,9 @@ __device__ __forceinline__ void collide_block(const CollideArgs& __restrict__ a,
   const Geo& g = a.g;
   const T* __restrict__ S = static_cast<const T*>(src);
   T* __restrict__ D = static_cast<T*>(dst);
-  if (IBM && lb == 0) reduce_forces(a);
+  // the first block reduces the step's forces on its way, a wave per foil
+  if (IBM && lb == 0)
+    for (int w = (int)threadIdx.y; w < a.nw; w += kBlockRows) reduce_forces(a, w, (int)threadIdx.x);
   // Waves to (64-cell chunk, row).  FP32: a block is one chunk of 4
   // consecutive rows (tiles in XCD runs, below).  16-bit storage: waves run along x first, so the
   // chunks of a row sit in one block and the cache line each chunk shares
@@ -66,7 +68,7 @@ __device__ __forceinline__ void collide_block(const CollideArgs& __restrict__ a,
     // Bijective on the tiles; grouped launches keep the plain order.
     int lt = lb;
     const int G = (a.nxc >= 8 ? 8 : 4) * a.nxc;
-    const int M = (int)(gridDim.x / (8 * G)) * 8 * G;
+    const int M = a.nblocks / (8 * G) * 8 * G;
     if (lt < M && (int)gridDim.x == a.nblocks) {
       const int xcd = lt & 7, k = lt >> 3;
       lt = ((k / G) * 8 + xcd) * G + k % G;

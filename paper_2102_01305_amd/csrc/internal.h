@@ -83,7 +83,7 @@ struct CollideArgs {
   unsigned nxc_mul, ny_mul;
   double* mass_part;         // per-block partial sums (check steps); face blocks after nblocks
   int* flags;                // bit 0: non-finite density seen
-  // force reduction by block 0 on steps with foils
+  // force reduction on steps with foils
   const double* fpart;       // [nw][nz][4] layer forces and moments
   double* hist;              // [H][nw][8]
   long long hist_row;

@@ -161,7 +161,6 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
   const char* __restrict__ S = static_cast<const char*>(src);
   float* __restrict__ D = static_cast<float*>(dst);
   __shared__ ColumnBits cb;
-  if (IBM && lb == 0) reduce_forces(b);
   // each XCD takes one run of consecutive columns: neighbours share their
   // halo rows and lines through one L2
   const int per = nblocks >> 3;
@@ -367,6 +366,9 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
       hz = zw0 ? own(p, 17) : own(p, 15);
     }
   }
+  // step s+1's forces, by a wave that has had no step s+1 to take
+  if (IBM && lb == 0 && w == 0)
+    for (int k = 0; k < a.nw; ++k) reduce_forces(b, k, lane);
 }
 
 struct PairGroup {
@@ -422,8 +424,11 @@ template <bool FORCE, bool ZH>
 __device__ __forceinline__ void near_block(const CollideArgs& __restrict__ a, const CollideArgs& __restrict__ b,
                                            int lb, const void* src, void* dst) {
   const Geo& g = a.g;
-  if (lb == 0) reduce_forces(a);
-  int u = __builtin_amdgcn_readfirstlane(lb * kBlockRows + (int)threadIdx.y);
+  if (lb == 0) {                                       // (the first block: step s's forces)
+    for (int k = (int)threadIdx.y; k < a.nw; k += kBlockRows) reduce_forces(a, k, (int)threadIdx.x);
+    return;
+  }
+  int u = __builtin_amdgcn_readfirstlane((lb - 1) * kBlockRows + (int)threadIdx.y);
   for (int k = 0; k < a.nw; ++k) {
     int x0, y0, w, h;
     near_region(b.box[k], g, x0, y0, w, h);
@@ -469,7 +474,7 @@ hipError_t launch_near(bool force, bool zh, const CollideArgs* const* host, cons
       near_region(host[k][1].box[j], host[k]->g, x0, y0, w, h);
       waves += (long long)((w + kBlockX - 1) / kBlockX) * h * host[k]->g.nz;
     }
-    blocks[k] = (int)((waves + kBlockRows - 1) / kBlockRows);
+    blocks[k] = (int)((waves + kBlockRows - 1) / kBlockRows) + 1;
     g.src[k] = src[k];
     g.dst[k] = dst[k];
   }

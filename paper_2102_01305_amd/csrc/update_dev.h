@@ -215,41 +215,47 @@ __device__ __forceinline__ void store_cell(typename St::T* __restrict__ D, const
   }
 }
 
-// Block 0 of a collide launch after the marker kernels: per foil, the sum
-// over span layers of the layer forces and moments in a fixed order, the
-// coefficients (Sec. 3.6-3.7: lift is the lateral component, counted outward
-// for a mirrored pair; thrust is -F_x; drag = -thrust) and the history row.
-__device__ inline void reduce_forces(const CollideArgs& a) {
-  __shared__ double red[4][kBlockX * kBlockRows];
-  constexpr int nt = kBlockX * kBlockRows;           // (threads past these only wait)
-  const int t = threadIdx.y * blockDim.x + threadIdx.x;
-  for (int w = 0; w < a.nw; ++w) {
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    const double* fp = a.fpart + 4 * (size_t)w * a.g.nz;
-    if (t < nt) {
-      for (int l = t; l < a.g.nz; l += nt)
-        for (int k = 0; k < 4; ++k) v[k] += fp[4 * l + k];
-      for (int k = 0; k < 4; ++k) red[k][t] = v[k];
+// After the marker kernels of step `a`, one wave per foil w: the sum over span
+// layers of the layer forces and moments, the coefficients (Sec. 3.6-3.7: lift
+// is the lateral component, counted outward for a mirrored pair; thrust is
+// -F_x; drag = -thrust) and the history row.  The order is fixed: 256 partial
+// sums over the layers t, t + 256, ..., of which a lane holds four, then halves
+// added to halves.  In registers and lane shuffles, as a block of 256 threads
+// with the partial sums in LDS took 4 us, most of it barriers: the smallest
+// solves waited for it (collide 64x48x8 with two foils 9.4 -> 7.7 us).  (A
+// block of its own for it, no faster, made the 16-bit collide of 160x128x128
+// 5% slower.)
+__device__ __forceinline__ void reduce_forces(const CollideArgs& a, int w, int lane) {
+  const auto* fp = gmem(a.fpart) + 4 * (size_t)w * a.g.nz;
+  double F[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int q = 0; q < 2; ++q) {                        // partial sums q and q + 2 of the lane
+    double v[2][4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[j][k] = 0.0;
+      for (int l = lane + 64 * q + 128 * j; l < a.g.nz; l += 256)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[j][k] += fp[4 * l + k];
     }
-    __syncthreads();
-    for (int h = nt / 2; h > 0; h >>= 1) {
-      if (t < h)
-        for (int k = 0; k < 4; ++k) red[k][t] += red[k][t + h];
-      __syncthreads();
-    }
-    if (t == 0) {
-      const double F0 = red[0][0], F1 = red[1][0], F2 = red[2][0], F3 = red[3][0];
-      double* h = a.hist + ((size_t)a.hist_row * a.nw + w) * 8;
-      h[0] = F0;
-      h[1] = F1;
-      h[2] = F2;
-      h[3] = F3;
-      h[4] = -a.sense[w] * F1 / a.qS;
-      h[5] = -F0 / a.qS;
-      h[6] = F0 / a.qS;
-      h[7] = F3 / (a.qS * a.chord[w]);
-    }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) F[k] = q == 0 ? v[0][k] + v[1][k] : F[k] + (v[0][k] + v[1][k]);
+  }
+#pragma unroll
+  for (int h = 32; h > 0; h >>= 1)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) F[k] += __shfl_down(F[k], h);
+  if (lane == 0) {
+    double* h = a.hist + ((size_t)a.hist_row * a.nw + w) * 8;
+    h[0] = F[0];
+    h[1] = F[1];
+    h[2] = F[2];
+    h[3] = F[3];
+    h[4] = -a.sense[w] * F[1] / a.qS;
+    h[5] = -F[0] / a.qS;
+    h[6] = F[0] / a.qS;
+    h[7] = F[3] / (a.qS * a.chord[w]);
   }
 }
 
