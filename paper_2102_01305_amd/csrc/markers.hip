@@ -228,14 +228,25 @@ __global__ void __launch_bounds__(256) k_factor(Group gr) {
   factor_block<NT>(*a, lb);
 }
 
-// rho and u* = (sum c f + F_body/2)/rho (Eqs. 2, 9, 11) of the
-// pre-collision state at the support nodes of every foil's markers, on every
+// rho and u* = (sum c f + F_body/2)/rho (Eqs. 2, 9, 11) of the pre-collision
+// state at cell (x, y, z).
+template <class St>
+__device__ __forceinline__ float4 node_moments(const MarkerArgs& a, const void* src, int x, int y, int z) {
+  float f[kQ];
+  pull19<St>(static_cast<const typename St::T*>(src), a.g, x, y, z, f);
+  zou_he<St, false>(a.g, a.p, x, y, z, f);
+  float drho, jx, jy, jz;
+  moments19(f, drho, jx, jy, jz);
+  const float rho = 1.0f + drho;
+  return make_float4(rho, (jx + 0.5f * a.p.fb[0]) / rho, (jy + 0.5f * a.p.fb[1]) / rho, (jz + 0.5f * a.p.fb[2]) / rho);
+}
+
+// Those moments at the support nodes of every foil's markers, on every
 // layer.  One wave per 64 entries of a foil's support list on one layer;
 // waves past the list's length (the host sizes the grid from a bound) end at
 // once.
 template <class St>
 __device__ __forceinline__ void band_block(const MarkerArgs& __restrict__ a, int lb, const void* src) {
-  using T = typename St::T;
   int R = __builtin_amdgcn_readfirstlane((int)(lb * 4 + (threadIdx.x >> 6)));
   const int lane = threadIdx.x & 63;
   int wi = 0;
@@ -257,23 +268,17 @@ __device__ __forceinline__ void band_block(const MarkerArgs& __restrict__ a, int
   const unsigned cell = list[1 + (e < last ? e : last - 1)];
   if (e >= (int)cnt) return;
   const int lx = (int)(cell & 0xffffu), ly = (int)(cell >> 16);
-  float f[kQ];
-  pull19<St>(static_cast<const T*>(src), a.g, w.x0 + lx, w.y0 + ly, z, f);
-  zou_he<St, false>(a.g, a.p, w.x0 + lx, w.y0 + ly, z, f);
-  float drho, jx, jy, jz;
-  moments19(f, drho, jx, jy, jz);
-  const float rho = 1.0f + drho;
-  w.band[((long long)z * w.side + ly) * w.side + lx] =
-      make_float4(rho, (jx + 0.5f * a.p.fb[0]) / rho, (jy + 0.5f * a.p.fb[1]) / rho, (jz + 0.5f * a.p.fb[2]) / rho);
+  w.band[((long long)z * w.side + ly) * w.side + lx] = node_moments<St>(a, src, w.x0 + lx, w.y0 + ly, z);
 }
 
-struct BandGroup {
+// A grouped launch of kernels that read the lattice: its state per solve.
+struct SourceGroup {
   Group g;
   const void* src[kMaxGroup];
 };
 
 template <class St>
-__global__ void __launch_bounds__(256) k_band(BandGroup gr) {
+__global__ void __launch_bounds__(256) k_band(SourceGroup gr) {
   int lb;
   const int k = group_index(gr.g, lb);
   band_block<St>(*static_cast<const MarkerArgs*>(gr.g.args[k]), lb, gr.src[k]);
@@ -308,10 +313,19 @@ __host__ __device__ inline int parts_at(int ns, int threads) {
   return parts < 1 ? 1 : (parts > 8 ? 8 : parts);
 }
 
-// LDS of a block: G (2 ns), B (3 ns), partial sums (parts x 3 ns) and the
-// xy sums R (4 ns).
+// Longest span whose interpolation blocks pull the moments of their marker's
+// 16 nodes a layer themselves, with no band launch before them: a launch of
+// the smallest chain is 4 us of latency.  Neighbouring markers then pull most
+// nodes again, so it pays while half a block's threads take them in one turn.
+// Step of clap & fling in us, band launch / pulled: 64x48x8 27.3 / 24.0,
+// 96x80x16 28.9 / 27.5, 96x80x32 32.1 / 34.4, 96x80x48 36.0 / 41.3; 2D figure
+// eight 1000x500 38.7 / 35.3.
+constexpr int kPullSpan = 16;
+
+// LDS of a block: G (2 ns), B (3 ns), partial sums (parts x 3 ns), the
+// xy sums R (4 ns) and, where it pulls them, the nodes' moments (32 ns).
 __host__ __device__ inline size_t interp_span_doubles(int ns, int parts) {
-  const size_t d = (size_t)(9 + 3 * parts) * ns;
+  const size_t d = (size_t)(9 + 3 * parts + (ns <= kPullSpan ? 32 : 0)) * ns;
   return (d + 1) / 2 * 2;
 }
 __host__ __device__ inline size_t lds_at(int ns, int threads) {
@@ -328,7 +342,10 @@ __host__ __device__ inline int span_threads(int ns) { return lds_at(ns, 512) <= 
 __host__ __device__ inline int span_parts(int ns) { return parts_at(ns, span_threads(ns)); }
 __host__ __device__ inline size_t interp_span_lds(int ns) { return lds_at(ns, span_threads(ns)); }
 
-__device__ __forceinline__ void interp_span_block(const MarkerArgs& __restrict__ a, int lb) {
+// PULL: solves with spans up to kPullSpan are among the launch (without the
+// pull the kernel takes fewer registers: chain -0.6 us at 96x80x80).
+template <class St, bool PULL>
+__device__ __forceinline__ void interp_span_block(const MarkerArgs& __restrict__ a, int lb, const void* src) {
   extern __shared__ double lds[];
   // workgroups are dealt to the 8 XCDs in turn: blocks lb = 8 k + x take
   // the run of markers x * (M / 8) + k, so neighbouring markers, which
@@ -368,15 +385,29 @@ __device__ __forceinline__ void interp_span_block(const MarkerArgs& __restrict__
   const double thd = a.pose[wi][1], vx = a.pose[wi][4], vy = a.pose[wi][5];
   const double Ux = vx - thd * r[3], Uy = vy + thd * r[2];
   {
-    // the 16 band records of layer z, loaded together straight from L2
+    // the 16 band records of layer z, loaded together straight from L2, or
+    // made here
     const int bx = (int)r[12] - w.x0, by = (int)r[13] - w.y0;
     typedef float v4f __attribute__((ext_vector_type(4)));   // one 16-byte load per record
     const auto* band = gmem(reinterpret_cast<const v4f*>(w.band));
+    const bool pull = PULL && ns <= kPullSpan;
+    float4* nodes = reinterpret_cast<float4*>(R + 4 * ns);   // 16 per layer
+    if (pull) {
+      for (int e = threadIdx.x; e < 16 * ns; e += bd)
+        nodes[e] = node_moments<St>(a, src, (int)r[12] + (e & 3), (int)r[13] + ((e >> 2) & 3), e >> 4);
+      __syncthreads();
+    }
     for (int z = threadIdx.x; z < ns; z += bd) {
-      const auto* row0 = band + ((long long)z * w.side + by) * w.side + bx;
       v4f v[16];
+      if (pull) {
+        const v4f* mine = reinterpret_cast<const v4f*>(nodes) + 16 * z;
 #pragma unroll
-      for (int node = 0; node < 16; ++node) v[node] = row0[(node >> 2) * w.side + (node & 3)];
+        for (int node = 0; node < 16; ++node) v[node] = mine[node];
+      } else {
+        const auto* row0 = band + ((long long)z * w.side + by) * w.side + bx;
+#pragma unroll
+        for (int node = 0; node < 16; ++node) v[node] = row0[(node >> 2) * w.side + (node & 3)];
+      }
       double R0 = 0.0, R1 = 0.0, R2 = 0.0, R3 = 0.0;
 #pragma unroll
       for (int oy = 0; oy < 4; ++oy) {
@@ -464,10 +495,11 @@ __device__ __forceinline__ void interp_span_block(const MarkerArgs& __restrict__
   }
 }
 
-__global__ void __launch_bounds__(512) k_interp_span(Group gr) {
+template <class St, bool PULL>
+__global__ void __launch_bounds__(512) k_interp_span(SourceGroup gr) {
   int lb;
-  const MarkerArgs* a = static_cast<const MarkerArgs*>(group_find(gr, lb));
-  interp_span_block(*a, lb);
+  const int k = group_index(gr.g, lb);
+  interp_span_block<St, PULL>(*static_cast<const MarkerArgs*>(gr.g.args[k]), lb, gr.src[k]);
 }
 
 // Block (foil, span layer s): the perimeter part of the solve,
@@ -622,6 +654,7 @@ hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   int nb[kMaxGroup], nl[kMaxGroup], np[kMaxGroup];
   size_t lds_l = 0, lds_s = 0;
+  bool pull = false;
   for (int j = 0; j < n; ++j) {
     const MarkerArgs& a = *host[j];
     int maxnp = 0, layers = 0, perims = 0, maxcells = 0;
@@ -634,7 +667,9 @@ hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void
     }
     const size_t ll = (size_t)(kPw + 6) * maxnp * sizeof(double) + (size_t)a.copies * maxcells * 3 * sizeof(float);
     lds_l = ll > lds_l ? ll : lds_l;
-    nb[j] = a.band_blocks;   // 4 waves per block, 64 support-list entries per wave
+    // 4 waves per block, 64 support-list entries per wave
+    nb[j] = a.g.nz <= kPullSpan ? 0 : a.band_blocks;
+    pull = pull || a.g.nz <= kPullSpan;
     nl[j] = layers;
     np[j] = perims;
   }
@@ -645,10 +680,14 @@ hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void
     const size_t ls = interp_span_lds(host[j]->g.nz);
     lds_s = ls > lds_s ? ls : lds_s;
   }
+  void (*const interp)(SourceGroup) = !pull                ? k_interp_span<StF32, false>
+                                      : storage == ST_F32 ? k_interp_span<StF32, true>
+                                      : storage == ST_F16 ? k_interp_span<StF16, true>
+                                                          : k_interp_span<StBF16, true>;
   hipError_t e = raise_lds(reinterpret_cast<const void*>(k_layer), lds_l);
-  if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(k_interp_span), lds_s);
+  if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(interp), lds_s);
   if (e != hipSuccess) return e;
-  BandGroup bg;
+  SourceGroup bg;
   Group& g = bg.g;
   for (int j = 0; j < n; ++j) bg.src[j] = src[j];
   int total = group_fill(g, dev, nb, n);
@@ -663,7 +702,7 @@ hipError_t launch_markers(int storage, const MarkerArgs* const* host, const void
   }
   const int tp = group_fill(g, dev, np, n);
   if (tp == 0) return hipSuccess;
-  k_interp_span<<<tp, thr, lds_s, s>>>(g);
+  interp<<<tp, thr, lds_s, s>>>(bg);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   total = group_fill(g, dev, nl, n);
