@@ -22,9 +22,11 @@
  *  - Device memory is owned by the caller: one workspace of at least
  *    ibmlbm_workspace_bytes() bytes, 256-byte aligned, handed to create().
  *    The library never allocates device memory.  The library owns only the
- *    host-side handle and, per handle, a small pinned host buffer (about
- *    150 KB) through which it uploads the launch arguments of 64 steps at a
- *    time.  Input arrays are copied, never retained.
+ *    host-side handle and, per handle, pinned host memory: a small buffer
+ *    (about 210 KB) through which it uploads the launch arguments of 64 steps
+ *    at a time and returns force rows, and, from the first call that moves a
+ *    whole field on, up to 16 MB of staging, given back by destroy.  Input
+ *    arrays are copied, never retained.
  *  - Work is enqueued on the caller's HIP stream (hipStream_t passed as
  *    void*; NULL = the null stream).  step() only enqueues; forces(),
  *    fields(), mass() and destroy() synchronise the stream.  A device error
@@ -233,7 +235,8 @@ IBMLBM_API int ibmlbm_forces(ibmlbm_t h, int64_t first, int64_t count, double* o
  * u* = (sum_i c_i f_i + F_body/2)/rho of Eqs. 2, 9 and 11, of the streamed
  * distributions the next step starts from, before its IBM correction),
  * FDIST (19N: the post-collision state f* of Eq. 7, canonical order).
- * Synchronises the stream; RHO and U use the other state buffer as scratch.
+ * Synchronises the stream and uses the other state buffer as scratch; large
+ * fields are converted by up to 8 host threads that end with the call.
  * ESTATE before init_fields, EINVAL for an unknown field. */
 IBMLBM_API int ibmlbm_fields(ibmlbm_t h, int32_t which, double* out);
 

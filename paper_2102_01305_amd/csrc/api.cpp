@@ -4,11 +4,13 @@
 #include "ibmlbm.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "divmul.h"
@@ -56,6 +58,13 @@ struct WingGeom {
 
 constexpr int kPwStride = 14;      // doubles per perimeter record (markers.hip)
 
+// Field transfers between device floats and the caller's doubles: chunks of
+// one slot each, converted by up to kSlots host threads.  The link moves
+// 54 GB/s through pinned memory, one thread converts into fresh pages at
+// 17 GB/s, eight at 60.
+constexpr int kSlots = 8;
+constexpr size_t kSlotBytes = size_t(2) << 20;
+
 struct MarkerLayout {
   Region ref, G, Minv, pw, sup, T, X, U, B, rhoB, duB, fpart, hist;
   std::vector<Region> band, corr;
@@ -92,9 +101,14 @@ struct ibmlbm_s {
   long long win_t0 = -1;            // window of precomputed factors and launch arguments
   std::vector<CollideArgs> wca;     // host copies of the window's arguments
   std::vector<MarkerArgs> wma;
-  void* pin = nullptr;              // pinned staging of the window upload
+  void* pin = nullptr;              // pinned staging of the window upload, then of force rows
   hipEvent_t pin_ev = nullptr;      // completes when the last upload has been read
   bool pin_pending = false;
+  // pinned staging of field transfers, a slot per thread that moves them (made
+  // with the first such transfer, given back with the handle)
+  void* slot[kSlots] = {};
+  hipEvent_t slot_ev[kSlots] = {};
+  int slots = 0;
   // timing
   bool timing = false;
   int timing_every = 1;             // bracket one step in this many
@@ -791,6 +805,90 @@ int fill_window(ibmlbm_t h, long long s0) {
   return IBMLBM_OK;
 }
 
+// Pinned slots for up to n threads; how many there are (0 for handles that
+// must not allocate, or where there is no pinned memory left).
+int ensure_slots(ibmlbm_t h, int n) {
+  while (!h->noalloc && h->slots < n) {
+    void* p = nullptr;
+    hipEvent_t ev = nullptr;
+    if (hipHostMalloc(&p, kSlotBytes, hipHostMallocDefault) != hipSuccess ||
+        hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      if (p) (void)hipHostFree(p);
+      break;
+    }
+    h->slot[h->slots] = p;
+    h->slot_ev[h->slots++] = ev;
+  }
+  return std::min(n, h->slots);
+}
+
+// Move n floats between `dev` and the host on h's stream, chunk by chunk:
+// fn(begin, count, buf) fills buf before its upload (up) or takes it after its
+// download.  Returns when all are moved.
+template <class F>
+int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
+  const size_t chunk = kSlotBytes / sizeof(float), chunks = (n + chunk - 1) / chunk;
+  if (n == 0) return IBMLBM_OK;
+  const unsigned cores = std::max(1u, std::thread::hardware_concurrency());
+  int device = 0;
+  HIP_TRY(h, hipGetDevice(&device));
+  const int want = (int)std::min<size_t>({chunks, (size_t)kSlots, (size_t)cores});
+  const int have = ensure_slots(h, want);
+  std::vector<float> plain;                            // staging where there is no pinned memory
+  if (have == 0) {
+    try {
+      plain.resize(std::min(n, chunk));
+    } catch (...) {
+      return fail(h, IBMLBM_ENOMEM, "no host memory for a field transfer");
+    }
+  }
+  std::atomic<size_t> next{0};
+  std::atomic<int> err{hipSuccess};
+  auto work = [&](int t) {
+    if (t > 0 && hipSetDevice(device) != hipSuccess) return;
+    float* buf = have == 0 ? plain.data() : static_cast<float*>(h->slot[t]);
+    for (size_t c; err.load() == hipSuccess && (c = next.fetch_add(1)) < chunks;) {
+      const size_t begin = c * chunk, count = std::min(chunk, n - begin);
+      if (up) fn(begin, count, buf);
+      void* to = up ? static_cast<void*>(dev + begin) : buf;
+      const void* from = up ? buf : static_cast<const void*>(dev + begin);
+      hipError_t e = hipMemcpyAsync(to, from, count * sizeof(float), up ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost,
+                                    h->stream);
+      if (have == 0) {
+        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+      } else {
+        if (e == hipSuccess) e = hipEventRecord(h->slot_ev[t], h->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(h->slot_ev[t]);
+      }
+      if (e != hipSuccess)
+        err.store(e);
+      else if (!up)
+        fn(begin, count, buf);
+    }
+  };
+  std::thread hands[kSlots];
+  try {
+    for (int t = 1; t < have; ++t) hands[t] = std::thread(work, t);
+  } catch (...) {
+    // no more threads to be had: those there are take all chunks
+  }
+  work(0);
+  for (auto& t : hands)
+    if (t.joinable()) t.join();
+  const hipError_t e = (hipError_t)err.load();
+  if (e != hipSuccess) return fail(h, IBMLBM_EDEVICE, "field transfer failed: %s", hipGetErrorString(e));
+  return IBMLBM_OK;
+}
+
+// Lattice weight w_q.
+double weight(int q) { return q == 0 ? 1.0 / 3 : (q < 7 ? 1.0 / 18 : 1.0 / 36); }
+
+// Populations of every cell that fit as dense floats in a state buffer.
+int dense_populations(ibmlbm_t h) {
+  return (int)std::min<size_t>(kQ, h->L.fB.bytes / (h->L.N * sizeof(float)));
+}
+
 bool has_force(const ibmlbm_config& c) {
   return c.body_force[0] != 0.0 || c.body_force[1] != 0.0 || c.body_force[2] != 0.0;
 }
@@ -1079,7 +1177,7 @@ int create_handle(const ibmlbm_config* cfg, void* dev_buf, size_t bytes, void* h
   // solve's contents)
   hipError_t e = hipMemsetAsync(h->sb + L.diag.off, 0, L.diag.bytes, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  if (e == hipSuccess && !noalloc) e = hipHostMalloc(&h->pin, L.argtab.bytes, hipHostMallocDefault);
+  if (e == hipSuccess && !noalloc) e = hipHostMalloc(&h->pin, L.argtab.bytes + kExportDoubles * 8 + 8, hipHostMallocDefault);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&h->pin_ev, hipEventDisableTiming);
   if (e != hipSuccess) {
     int r = fail(nullptr, IBMLBM_EDEVICE, "create failed: %s", hipGetErrorString(e));
@@ -1123,33 +1221,23 @@ int ibmlbm_init_fields(ibmlbm_t h, const double* rho, const double* u, const dou
   h->cur_is_A = true;
   void* dst = h->ws + L.fA.off;
   if (fdist) {
-    // pack f_i - w_i into the padded layout on the host
-    const double w[kQ] = {1.0 / 3, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18,
-                          1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36,
-                          1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
-    std::vector<unsigned char> host(L.total * L.es, 0);
-    const int nx = h->cfg.nx, ny = h->cfg.ny, nz = h->cfg.nz;
-    for (int q = 0; q < kQ; ++q)
-      for (int z = 0; z < nz; ++z)
-        for (int y = 0; y < ny; ++y)
-          for (int x = 0; x < nx; ++x) {
-            const size_t cell = ((size_t)z * ny + y) * nx + x;
-            const float v = (float)(fdist[(size_t)q * N + cell] - w[q]);
-            const size_t idx = (((size_t)(z * ny + y) + 1) * kQ + q) * L.px + x;
-            if (L.es == 4) {
-              std::memcpy(&host[idx * 4], &v, 4);
-            } else if (h->cfg.storage == IBMLBM_FP16_DEV) {
-              _Float16 hv = (_Float16)(v * kF16Scale);
-              std::memcpy(&host[idx * 2], &hv, 2);
-            } else {
-              uint32_t u32;
-              std::memcpy(&u32, &v, 4);
-              u32 += 0x7fffu + ((u32 >> 16) & 1u);
-              const uint16_t b16 = (uint16_t)(u32 >> 16);
-              std::memcpy(&host[idx * 2], &b16, 2);
-            }
-          }
-    HIP_TRY(h, hipMemcpyAsync(dst, host.data(), host.size(), hipMemcpyHostToDevice, h->stream));
+    // f_i - w_i of as many populations as the other state buffer holds, dense
+    // in floats there, then into the padded layout in the stored type
+    float* dense = reinterpret_cast<float*>(h->ws + L.fB.off);
+    const int most = dense_populations(h);
+    for (int q0 = 0; q0 < kQ; q0 += most) {
+      const int nq = std::min(most, kQ - q0);
+      int rc = staged(h, dense, (size_t)nq * N, true, [&](size_t begin, size_t count, float* buf) {
+        for (size_t k = 0; k < count;) {
+          const size_t i = (size_t)q0 * N + begin + k, q = i / N, run = std::min(count - k, (q + 1) * N - i);
+          const double w = weight((int)q);
+          for (size_t j = 0; j < run; ++j) buf[k + j] = (float)(fdist[i + j] - w);
+          k += run;
+        }
+      });
+      if (rc) return rc;
+      HIP_TRY(h, launch_pack(h->cfg.storage, h->geo, dense, q0, nq, dst, h->stream));
+    }
     HIP_TRY(h, hipStreamSynchronize(h->stream));
   } else {
     // stage FP64 rho and u in the other state buffer (free between steps)
@@ -1277,17 +1365,28 @@ int ibmlbm_forces(ibmlbm_t h, int64_t first, int64_t count, double* out) {
     return fail(h, IBMLBM_ERANGE, "history rows [%lld, %lld) not held (have [%lld, %lld))",
                 (long long)first, (long long)(first + count), (long long)std::max(0LL, h->step - H),
                 (long long)h->step);
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
   int flags = 0;
-  HIP_TRY(h, hipMemcpy(&flags, h->sb + h->L.diag.off + 16, 4, hipMemcpyDeviceToHost));
   const size_t row = (size_t)h->nw * 8;
   const double* hist = at<double>(h, h->M.hist);
-  // the rows form at most two contiguous runs of the ring
-  for (long long k = 0; k < count;) {
-    const long long r = (first + k) % H;
-    const long long run = std::min<long long>(count - k, H - r);
-    HIP_TRY(h, hipMemcpy(out + k * row, hist + r * row, (size_t)run * row * 8, hipMemcpyDeviceToHost));
-    k += run;
+  const int* dflags = reinterpret_cast<const int*>(h->sb + h->L.diag.off + 16);
+  if (h->pin && (size_t)count * row <= kExportDoubles) {
+    // a few rows, as a control loop asks for them: one kernel writes them and
+    // the flags to pinned memory (two blocking copies took 39 us)
+    double* rows = reinterpret_cast<double*>(static_cast<char*>(h->pin) + h->L.argtab.bytes);
+    HIP_TRY(h, launch_export(hist, first % H, H, (int)((size_t)count * row), (int)row, dflags, rows, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (count > 0) std::memcpy(out, rows, (size_t)count * row * 8);
+    std::memcpy(&flags, rows + kExportDoubles, 4);
+  } else {
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    HIP_TRY(h, hipMemcpy(&flags, dflags, 4, hipMemcpyDeviceToHost));
+    // the rows form at most two contiguous runs of the ring
+    for (long long k = 0; k < count;) {
+      const long long r = (first + k) % H;
+      const long long run = std::min<long long>(count - k, H - r);
+      HIP_TRY(h, hipMemcpy(out + k * row, hist + r * row, (size_t)run * row * 8, hipMemcpyDeviceToHost));
+      k += run;
+    }
   }
   if (flags & 4) return fail(h, IBMLBM_EDEVICE, "a foil's support nodes outnumbered the band grid sized for them");
   if (flags & 2) return fail(h, IBMLBM_EDIVERGED, "a perimeter system became singular");
@@ -1301,47 +1400,30 @@ int ibmlbm_fields(ibmlbm_t h, int32_t which, double* out) {
   if (!h->initialized) return fail(h, IBMLBM_ESTATE, "fields before init_fields");
   const LatticeLayout& L = h->L;
   const size_t N = L.N;
-  const int nx = h->cfg.nx, ny = h->cfg.ny, nz = h->cfg.nz;
   if (which == IBMLBM_FIELD_RHO || which == IBMLBM_FIELD_U) {
     float* scratch = static_cast<float*>(next_state(h));
     HIP_TRY(h, launch_moments(h->cfg.storage, h->geo, h->phys, cur_state(h), scratch, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    std::vector<float> host(4 * N);
-    HIP_TRY(h, hipMemcpy(host.data(), scratch, 4 * N * sizeof(float), hipMemcpyDeviceToHost));
-    if (which == IBMLBM_FIELD_RHO)
-      for (size_t i = 0; i < N; ++i) out[i] = host[i];
-    else
-      for (size_t i = 0; i < 3 * N; ++i) out[i] = host[N + i];
-    return IBMLBM_OK;
+    const bool u = which == IBMLBM_FIELD_U;
+    return staged(h, u ? scratch + N : scratch, u ? 3 * N : N, false, [&](size_t begin, size_t count, const float* buf) {
+      for (size_t j = 0; j < count; ++j) out[begin + j] = buf[j];
+    });
   }
   if (which != IBMLBM_FIELD_FDIST) return fail(h, IBMLBM_EINVAL, "unknown field %d", which);
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
-  std::vector<unsigned char> host(L.total * L.es);
-  HIP_TRY(h, hipMemcpy(host.data(), cur_state(h), host.size(), hipMemcpyDeviceToHost));
-  const double w[kQ] = {1.0 / 3, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18,
-                        1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36,
-                        1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
-  for (int q = 0; q < kQ; ++q)
-    for (int z = 0; z < nz; ++z)
-      for (int y = 0; y < ny; ++y)
-        for (int x = 0; x < nx; ++x) {
-          const size_t cell = ((size_t)z * ny + y) * nx + x;
-          const size_t idx = (((size_t)(z * ny + y) + 1) * kQ + q) * L.px + x;
-          float v;
-          if (L.es == 4) {
-            std::memcpy(&v, &host[idx * 4], 4);
-          } else if (h->cfg.storage == IBMLBM_FP16_DEV) {
-            _Float16 hv;
-            std::memcpy(&hv, &host[idx * 2], 2);
-            v = (float)hv * kF16Unscale;
-          } else {
-            uint16_t b16;
-            std::memcpy(&b16, &host[idx * 2], 2);
-            const uint32_t u32 = (uint32_t)b16 << 16;
-            std::memcpy(&v, &u32, 4);
-          }
-          out[(size_t)q * N + cell] = w[q] + (double)v;
-        }
+  float* dense = static_cast<float*>(next_state(h));
+  const int most = dense_populations(h);
+  for (int q0 = 0; q0 < kQ; q0 += most) {
+    const int nq = std::min(most, kQ - q0);
+    HIP_TRY(h, launch_unpack(h->cfg.storage, h->geo, cur_state(h), q0, nq, dense, h->stream));
+    int rc = staged(h, dense, (size_t)nq * N, false, [&](size_t begin, size_t count, const float* buf) {
+      for (size_t k = 0; k < count;) {
+        const size_t i = (size_t)q0 * N + begin + k, q = i / N, run = std::min(count - k, (q + 1) * N - i);
+        const double w = weight((int)q);
+        for (size_t j = 0; j < run; ++j) out[i + j] = w + (double)buf[k + j];
+        k += run;
+      }
+    });
+    if (rc) return rc;
+  }
   return IBMLBM_OK;
 }
 
@@ -1432,6 +1514,10 @@ int ibmlbm_destroy(ibmlbm_t h) {
   for (auto& ev : h->ev) (void)hipEventDestroy(ev);
   if (h->pin_ev) (void)hipEventDestroy(h->pin_ev);
   if (h->pin) (void)hipHostFree(h->pin);
+  for (int t = 0; t < h->slots; ++t) {
+    (void)hipEventDestroy(h->slot_ev[t]);
+    (void)hipHostFree(h->slot[t]);
+  }
   delete h;
   if (e != hipSuccess) return fail(nullptr, IBMLBM_EDEVICE, "stream error at destroy: %s", hipGetErrorString(e));
   return IBMLBM_OK;

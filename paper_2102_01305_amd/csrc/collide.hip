@@ -272,6 +272,59 @@ hipError_t launch_moments(int storage, const Geo& g, const Phys& p, const void* 
   return hipGetLastError();
 }
 
+// Checkpoints: the stored populations as dense float planes of f - w, and
+// back, one thread per cell (reads and writes run along x in both).
+template <class St, bool PACK>
+__global__ void k_dense(Geo g, float* dense, int q0, int nq, typename St::T* state) {
+  const size_t N = (size_t)g.nx * g.ny * g.nz;
+  const size_t cell = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (cell >= N) return;
+  const int x = (int)(cell % g.nx);
+  const size_t r = cell / g.nx;
+  const int y = (int)(r % g.ny), z = (int)(r / g.ny);
+  typename St::T* own = state + rowbase(g, y, z) + x;
+  for (int q = 0; q < nq; ++q) {
+    typename St::T* p = own + (long long)(q0 + q) * g.ps;
+    if (PACK)
+      St::st(p, dense[q * N + cell]);
+    else
+      dense[q * N + cell] = St::ld(p);
+  }
+}
+
+template <bool PACK>
+static hipError_t launch_dense(int storage, const Geo& g, float* dense, int q0, int nq, void* state, hipStream_t s) {
+  const size_t N = (size_t)g.nx * g.ny * g.nz;
+  const unsigned nb = (unsigned)((N + 255) / 256);
+  switch (storage) {
+    case ST_F32: k_dense<StF32, PACK><<<nb, 256, 0, s>>>(g, dense, q0, nq, static_cast<float*>(state)); break;
+    case ST_F16: k_dense<StF16, PACK><<<nb, 256, 0, s>>>(g, dense, q0, nq, static_cast<__half*>(state)); break;
+    default: k_dense<StBF16, PACK><<<nb, 256, 0, s>>>(g, dense, q0, nq, static_cast<unsigned short*>(state)); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_pack(int storage, const Geo& g, const float* dense, int q0, int nq, void* state, hipStream_t s) {
+  return launch_dense<true>(storage, g, const_cast<float*>(dense), q0, nq, state, s);
+}
+
+hipError_t launch_unpack(int storage, const Geo& g, const void* state, int q0, int nq, float* dense,
+                         hipStream_t s) {
+  return launch_dense<false>(storage, g, dense, q0, nq, const_cast<void*>(state), s);
+}
+
+__global__ void k_export(const double* hist, long long first, long long ring, int n, int row, const int* flags,
+                         double* out) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = hist[((first + i / row) % ring) * row + i % row];
+  if (threadIdx.x == 0) *reinterpret_cast<int*>(out + kExportDoubles) = *flags;
+}
+
+hipError_t launch_export(const double* hist, long long first, long long ring, int n, int row, const int* flags,
+                         double* out, hipStream_t s) {
+  k_export<<<1, 256, 0, s>>>(hist, first, ring, n, row, flags, out);
+  return hipGetLastError();
+}
+
 __global__ void k_mass_reduce(const double* part, int n, double ncells, double* out, long long step) {
   __shared__ double sh[256];
   double s = 0.0;

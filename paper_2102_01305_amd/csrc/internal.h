@@ -137,6 +137,17 @@ hipError_t launch_mass_reduce(const double* part, int n, double ncells, double* 
                               long long step, hipStream_t s);
 constexpr size_t kMaxLds = 160 * 1024;  // LDS per block on gfx950
 
+// Populations q0 .. q0 + nq - 1 between a state and dense float planes of
+// f - w ([population][cell], x fastest), as the checkpoint calls move them.
+hipError_t launch_pack(int storage, const Geo& g, const float* dense, int q0, int nq, void* state, hipStream_t s);
+hipError_t launch_unpack(int storage, const Geo& g, const void* state, int q0, int nq, float* dense,
+                         hipStream_t s);
+// n values of the force-history ring from row `first` on and the status flags
+// into pinned host memory (the flags after kExportDoubles values).
+hipError_t launch_export(const double* hist, long long first, long long ring, int n, int row, const int* flags,
+                         double* out, hipStream_t s);
+constexpr size_t kExportDoubles = 4096;
+
 // Static scratch of ibmlbm_create_noalloc (scratch.hip): its size, and the
 // device address of a device's copy (looked up once per device).
 constexpr size_t kScratchBytes = size_t(64) << 20;
