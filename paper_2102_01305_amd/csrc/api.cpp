@@ -911,7 +911,8 @@ bool check_step(const ibmlbm_config& c, long long s) {
 // n_y slabs of their z with 31-bit offsets.
 bool pair_shape(ibmlbm_t h) {
   const ibmlbm_config& c = h->cfg;
-  return c.storage == IBMLBM_FP32 && c.nz >= 4 && (long long)c.ny * kQ * h->L.px * h->L.es < (1LL << 31);
+  return c.storage == IBMLBM_FP32 && c.nz >= 4 && (long long)c.ny * kQ * h->L.px * h->L.es < (1LL << 31) &&
+         (long long)c.ny * c.nz * 64 < (1LL << 31);
 }
 
 // Planes along y per block (`planes[j]`) of the solves of a call that take

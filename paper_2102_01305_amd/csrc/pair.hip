@@ -42,7 +42,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_rsrc(char* base) {
 // then take the ghost record or their own opposite population instead.
 template <bool ROW>
 __device__ __forceinline__ void pull_plane(const char* __restrict__ S, const Geo& g, const __amdgpu_buffer_rsrc_t rz[3],
-                                           unsigned popb, bool edge, int x, int y, int z, float f[kQ]) {
+                                           __amdgpu_buffer_rsrc_t rg, unsigned popb, bool edge, int x, int y, int z, float f[kQ]) {
   constexpr int es = sizeof(float);
   const unsigned rowb = (unsigned)kQ * popb;
   const int ys[3] = {y == 0 ? g.ny - 1 : y - 1, y, y == g.ny - 1 ? 0 : y + 1};   // y - c_y
@@ -65,14 +65,14 @@ __device__ __forceinline__ void pull_plane(const char* __restrict__ S, const Geo
     }
   }
   if (edge && (x == 0 || x == g.nx - 1)) {
-    constexpr int per = 32 / es;
-    const float* gb = reinterpret_cast<const float*>(S + g.goff);
+    // (a row's ghost records by its scalar offset: a record's address made in
+    // each lane took 40 vector operations a face)
 #pragma unroll
     for (int i = 0; i < kQ; ++i) {
       if (cxq(i) == 0) continue;
-      const long long gr = (long long)(zs[1 - czq(i)] * g.ny + ys[1 - cyq(i)]);
+      const int gr = zs[1 - czq(i)] * g.ny + ys[1 - cyq(i)] + (cxq(i) == 1 ? 0 : g.ny * g.nz);
       if (cxq(i) == 1 ? x == 0 : x == g.nx - 1)
-        f[i] = *(gb + ((cxq(i) == 1 ? 0LL : (long long)g.ny * g.nz) + gr) * per + xslot(i));
+        f[i] = ROW ? StF32::ldb(rg, 0, gr * 32 + xslot(i) * es) : StF32::ldb(rg, gr * 32 + xslot(i) * es, 0);
     }
   }
   const int wy = g.yper ? 0 : (y == 0 ? 1 : (y == g.ny - 1 ? -1 : 0));
@@ -161,6 +161,7 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
   const char* __restrict__ S = static_cast<const char*>(src);
   float* __restrict__ D = static_cast<float*>(dst);
   __shared__ ColumnBits cb;
+  __shared__ float face[2][2][R][kQ + 1];              // by parity: step s+1 at the x faces, per side and row
   // each XCD takes one run of consecutive columns: neighbours share their
   // halo rows and lines through one L2
   const int per = nblocks >> 3;
@@ -199,13 +200,19 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
   act = act && r <= cnt + 1 && (g.zper || (z >= 0 && z < g.nz));
   z = z < 0 ? z + g.nz : (z >= g.nz ? z - g.nz : z);
   const int zu = __builtin_amdgcn_readfirstlane(z);    // the row's z, for the compiler wave-uniform
-  const bool inner = !halo && w >= 1 && w <= cnt;      // rows that take step s+1
-  const bool xw0 = inner && g.bclo == BC_WALL && x0 == 0, xw1 = inner && g.bchi == BC_WALL && xe == g.nx;
-  const bool zw0 = inner && !g.zper && zu == 0, zw1 = inner && !g.zper && zu == g.nz - 1;
+  // what the wave's row is, in one scalar (a flag each would take two)
+  enum : int { kHalo = 1, kInner = 2, kXw0 = 4, kXw1 = 8, kZw0 = 16, kZw1 = 32, kWalls = 60, kEdge = 64 };
+  const bool takes2 = !halo && w >= 1 && w <= cnt;     // rows that take step s+1
+  int is = (halo ? kHalo : 0) | (x0 == 0 || xe >= g.nx - 1 ? kEdge : 0);   // (lanes lie at an x face)
+  if (takes2)
+    is |= kInner | (g.bclo == BC_WALL && x0 == 0 ? kXw0 : 0) | (g.bchi == BC_WALL && xe == g.nx ? kXw1 : 0) |
+          (!g.zper && zu == 0 ? kZw0 : 0) | (!g.zper && zu == g.nz - 1 ? kZw1 : 0);
+  is = __builtin_amdgcn_readfirstlane(is);
   const unsigned popb0 = (unsigned)g.px * (unsigned)sizeof(float);
   // descriptors of the three z that a row of lanes pulls from, and of the row
   // it writes
   __amdgpu_buffer_rsrc_t rz[3], rd;
+  const __amdgpu_buffer_rsrc_t rg = span_rsrc(const_cast<char*>(S) + g.goff);   // x-face ghost records
   {
     const unsigned long long slab = (unsigned long long)(kQ * popb0);
     const int zl = zu == 0 ? g.nz - 1 : zu - 1, zh = zu == g.nz - 1 ? 0 : zu + 1;
@@ -214,8 +221,6 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
     rz[2] = span_rsrc(const_cast<char*>(S) + (unsigned)(zh * g.ny + 1) * slab);
     rd = span_rsrc(reinterpret_cast<char*>(D) + (unsigned)(zu * g.ny + 1) * slab);
   }
-  const bool edge = x0 == 0 || xe >= g.nx - 1;         // lanes of the column lie at an x face
-  const bool walls = xw0 || xw1 || zw0 || zw1;
 
   // planes whose cells in this column may have a correction (a foil's node
   // boxes of both steps, and the plane after for step s+1; a periodic y axis
@@ -253,8 +258,8 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
   auto from = [&](int p, int i) { return shm[p & 1][lslot(i)][w - czq(i)][lane + 1 - cxq(i)]; };
   auto own = [&](int p, int i) { return shm[p & 1][lslot(i)][w][lane + 1]; };
 
-  // step s's pulled values of the next plane, fetched while the plane before
-  // is still worked on
+  // step s's values of a plane: pulled while the plane before is still worked
+  // on, updated in place, exchanged
   float nf[kQ];
   auto inside = [&](int p) { return g.yper || (p >= 0 && p < g.ny); };
   auto pull = [&](int p) {
@@ -263,10 +268,23 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
     unsigned popb = popb0;
     asm volatile("" : "+s"(popb));
     const int y = p < 0 ? p + g.ny : (p >= g.ny ? p - g.ny : p);
-    if (!halo)
-      pull_plane<true>(S, g, rz, popb, edge, x, y, zu, nf);
+    if (!(is & kHalo))
+      pull_plane<true>(S, g, rz, rg, popb, is & kEdge, x, y, zu, nf);
     else
-      pull_plane<false>(S, g, rz, popb, edge, x, y, z, nf);
+      pull_plane<false>(S, g, rz, rg, popb, is & kEdge, x, y, z, nf);
+  };
+  // The ghost records of plane q - 1, whose cells at the x faces were exchanged
+  // in iteration q: by a wave that takes no step s+1, a lane per side and row
+  // (in the waves of the rows, one lane of 64 took them a third of their time).
+  auto ghosts = [&](int q) {
+    const int side = lane >> 5, row = lane & 31;
+    const int fx = side ? g.nx - 1 : 0;
+    if (row < cnt && (side ? xe == g.nx : x0 == 0)) {
+      float v[kQ];
+#pragma unroll
+      for (int i = 0; i < kQ; ++i) v[i] = face[q & 1][side][row][i];
+      write_ghosts<StF32>(D, g, ph, fx, q - 1, z0 + row, v);
+    }
   };
   const int first = inside(ya - 1) ? ya - 1 : 0;
   if (act) pull(first);
@@ -276,28 +294,26 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
     Correction c2;                                     // of step s+1 at plane p-1
     if (real) {
       if (act) {
-        float f[kQ];
         const int y = p < 0 ? p + g.ny : (p >= g.ny ? p - g.ny : p);
         // both steps' corrections, while the pull is in flight
         Correction c;
-        if (IBM && p >= fy0 && p <= fy1) correction2(g, a, b, cb, ya - 1, col, x, p, true, inner && p > ya, z, c, c2);
-#pragma unroll
-        for (int i = 0; i < kQ; ++i) f[i] = nf[i];
-        update_cell<StF32, IBM, FORCE, ZH, true>(g, ph, a, x, y, z, f, c);
-        if (halo && kind != BC_PERIODIC) face_values(ph, kind, dir, f);
+        if (IBM && p >= fy0 && p <= fy1) correction2(g, a, b, cb, ya - 1, col, x, p, true, (is & kInner) && p > ya, z, c, c2);
+        update_cell<StF32, IBM, FORCE, ZH, true>(g, ph, a, x, y, z, nf, c);
+        if ((is & kHalo) && kind != BC_PERIODIC) face_values(ph, kind, dir, nf);
 #pragma unroll
         for (int i = 1; i < kQ; ++i)
-          if (i != 3 && i != 4) shm[p & 1][lslot(i)][r][col] = f[i];
-        o[0] = f[0];
-        o[1] = f[3];
-        o[2] = f[4];
+          if (i != 3 && i != 4) shm[p & 1][lslot(i)][r][col] = nf[i];
+        o[0] = nf[0];
+        o[1] = nf[3];
+        o[2] = nf[4];
         if (p < yb && inside(p + 1)) pull(p + 1);
       }
-      // one barrier a plane: what was read of this parity's buffer two planes
-      // ago was read before the last one
-      __syncthreads();
     }
-    if (!inner) continue;
+    // one barrier a plane: what was read of this parity's buffer two planes
+    // ago was read before the last one
+    __syncthreads();
+    if ((is & kEdge) && w == 0 && p > ya + 1) ghosts(p - 1);
+    if (!(is & kInner)) continue;
     if (p > ya) {
       float f[kQ];
 #pragma unroll
@@ -313,12 +329,12 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
         const int i = im[k];
         f[i] = sp[real ? (lslot(i) * (R + 2) - czq(i)) * LX - cxq(i) : lslot(oppq(i)) * (R + 2) * LX];
       }
-      if (walls && real) {
+      if ((is & kWalls) && real) {
         // reflected at the cell itself, from its own values of plane p-1
-        if (xw0 && x == 0) f[9] = hx;
-        if (xw1 && x == g.nx - 1) f[8] = hx;
-        if (zw0) f[18] = hz;
-        if (zw1) f[16] = hz;
+        if ((is & kXw0) && x == 0) f[9] = hx;
+        if ((is & kXw1) && x == g.nx - 1) f[8] = hx;
+        if (is & kZw0) f[18] = hz;
+        if (is & kZw1) f[16] = hz;
       }
       if (IBM && !real && p >= fy0 && p <= fy1) {
         Correction c;
@@ -331,7 +347,10 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
 #pragma unroll
         for (int i = 0; i < kQ; ++i)
           StF32::stb(rd, x * (int)sizeof(float), (int)((unsigned)((p - 1) * kQ + i) * popb), f[i]);
-        if (edge && (x == 0 || x == g.nx - 1)) write_ghosts<StF32>(D, g, ph, x, p - 1, zu, f);
+        if ((is & kEdge) && (x == 0 || x == g.nx - 1)) {
+#pragma unroll
+          for (int i = 0; i < kQ; ++i) face[p & 1][x != 0][w - 1][i] = f[i];
+        }
       }
     }
     // the values of plane p that the next two planes' updates pull
@@ -348,8 +367,9 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
     for (int k = 1; k < 9; ++k) h0[k] = from(p, i0[k]);
 #pragma unroll
     for (int k = 1; k < 5; ++k) pa[k] = from(p, ip[k]);
-    if (walls) {
-      const bool l0 = xw0 && x == 0, l1 = xw1 && x == g.nx - 1;
+    if (is & kWalls) {
+      const bool l0 = (is & kXw0) && x == 0, l1 = (is & kXw1) && x == g.nx - 1;
+      const bool zw0 = is & kZw0, zw1 = is & kZw1;
 #pragma unroll
       for (int k = 1; k < 9; ++k) {
         const int i = i0[k];
@@ -365,6 +385,10 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
       hx = x == 0 ? own(p, 10) : own(p, 7);
       hz = zw0 ? own(p, 17) : own(p, 15);
     }
+  }
+  if (is & kEdge) {
+    __syncthreads();
+    if (w == 0) ghosts(yb);
   }
   // step s+1's forces, by a wave that has had no step s+1 to take
   if (IBM && lb == 0 && w == 0)
