@@ -928,10 +928,10 @@ bool pair_shape(ibmlbm_t h) {
 //              most 40.
 // L is the one with the least march (the longer of two alike).
 // Measured (us for two steps, without markers, one by one / in pairs): 64^3
-// 24 / 28, 96x80x80 43 / 33, 128x96x96 69 / 46, 160x128x128 142 / 115,
-// 256x192x192 483 / 327, 512x384x384 3926 / 2455; with foils and their markers
-// 128x96x96 113 / 117, 160x128x128 191 / 226, 256x192x192 552 / 424; 6, 8 and
-// 16 solves of the sweep's four sizes together 389 / 406, 624 / 606, 1232 / 1123.
+// 24 / 28, 96x80x80 43 / 33, 128x96x96 69 / 47, 160x128x128 142 / 111,
+// 256x192x192 483 / 317, 512x384x384 3926 / 2415; with foils and their markers
+// 128x96x96 113 / 119, 160x128x128 191 / 221, 256x192x192 552 / 414; 6, 8 and
+// 16 solves of the sweep's four sizes together 389 / 387, 622 / 559, 1231 / 1008.
 void plan_pairs(ibmlbm_t* hs, int n, int steps, int* planes) {
   static const int lens[] = {64, 56, 48, 40, 32, 28, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4};
   for (int j = 0; j < n; ++j) planes[j] = 0;

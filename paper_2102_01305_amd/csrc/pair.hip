@@ -136,12 +136,13 @@ __device__ __forceinline__ void correction2(const Geo& g, const CollideArgs& a, 
 // and p-2 in the registers of the lane that uses them.
 //
 // Bound: memory, as for one step at a time, but the lattice is read and
-// written once for two steps: per launch 1.25 x the 76 B a cell that a read
+// written once for two steps: per launch 1.12 x the 76 B a cell that a read
 // takes (the rows and lines columns share, as far as one L2 does not serve
-// both) and 76 B written, 5.2 TB/s at 512x384x384 (periodic), with the vector
-// units busy 40% of the time.  Two steps of the collide kernel against one
-// launch here: 256x192x192 482 -> 327 us, 512x384x384 3926 -> 2455 us; clap &
-// fling 256x192x192 343 us, whole step 275 -> 214 us.
+// both) and 76 B written, 5.0 TB/s at 512x384x384 (periodic), with the vector
+// units busy 41% of the time.  Two steps of the collide kernel against one
+// launch here: 256x192x192 483 -> 317 us, 256x256x256 864 -> 592,
+// 512x384x384 3926 -> 2415; clap & fling 256x192x192 335 us (a plane that meets
+// a foil takes 2.4 us longer), whole step 275 -> 207 us.
 // Why this shape: one block per compute unit, so R as large as 16 waves and
 // 160 KB of LDS allow (halo work 1 + 3/R; 12 divides the spans in use); the
 // same with R = 7 or 8 and two blocks per unit 1262-1281 us a step at
@@ -443,11 +444,39 @@ hipError_t launch_pair(bool ibm, bool force, bool zh, const CollideArgs* const* 
 
 // ------------------------------------------------------------------- near --
 
-// One row of a foil's region (near_region of step s + 1) per wave.
+// Does a support node of foil box f lie at (x, y) or beside it?
+__device__ __forceinline__ bool near_support(const FoilBox& f, int x, int y) {
+  const int lx = x - 1 - f.x0, ly = y - f.y0, i = lx >> 5, sh = lx & 31;   // (i is -1 left of the box)
+  unsigned any = 0u;
+#pragma unroll
+  for (int d = -1; d <= 1; ++d) {
+    const int r = ly + d;
+    if (r < 0 || r >= f.h) continue;
+    const auto* row = gmem(f.bits) + r * f.words;
+    const unsigned lo = i >= 0 && i < f.words ? row[i] : 0u, hi = i + 1 < f.words ? row[i + 1] : 0u;
+    any |= sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
+  }
+  return any & 7u;
+}
+
+// Step s of the cells that step s + 1's marker kernels pull from: the support
+// nodes of that step and the cells beside them (k_pair overwrites every cell
+// afterwards).  A wave takes 64 cells of a foil's region (near_region of step
+// s + 1) of one layer, row after row: a row is some 25 to 50 cells long, so
+// that a wave per row left half of its lanes idle, and a third to a half of
+// the region lies inside the foil or in the corners, where no marker reads.
+// The stores are plain ones: the marker kernels read them next.  Bound by the
+// latency of its three rounds of dependent loads (bits, pull, correction).
+// Against a wave per row over the whole region with streaming stores: clap &
+// fling 256 x 192 x 192 21.0 -> 15.0 us (17.4 with streaming stores),
+// 512 x 384 x 384 50.8 -> 36.7, cylinder 256 x 192 x 192 15.6 -> 14.5; a step
+// of 16 solves of a sweep 523 -> 505.  The corrections' loads issued together
+// with the pull's gave nothing.
 template <bool FORCE, bool ZH>
 __device__ __forceinline__ void near_block(const CollideArgs& __restrict__ a, const CollideArgs& __restrict__ b,
                                            int lb, const void* src, void* dst) {
-  const Geo& g = a.g;
+  const Geo g = a.g;
+  const Phys& ph = a.p;
   if (lb == 0) {                                       // (the first block: step s's forces)
     for (int k = (int)threadIdx.y; k < a.nw; k += kBlockRows) reduce_forces(a, k, (int)threadIdx.x);
     return;
@@ -456,18 +485,47 @@ __device__ __forceinline__ void near_block(const CollideArgs& __restrict__ a, co
   for (int k = 0; k < a.nw; ++k) {
     int x0, y0, w, h;
     near_region(b.box[k], g, x0, y0, w, h);
-    const int nc = (w + kBlockX - 1) / kBlockX, units = nc * h * g.nz;
+    const int nc = (w * h + kBlockX - 1) / kBlockX, units = nc * g.nz;
     if (u >= units) {
       u -= units;
       continue;
     }
-    const int c = u % nc, row = u / nc, z = row / h, y = y0 + row - z * h;
-    const int lx = c * kBlockX + (int)threadIdx.x;
-    if (lx >= w) return;
+    const int z = __builtin_amdgcn_readfirstlane(u / nc);
+    const unsigned e = (unsigned)((u - z * nc) * kBlockX) + threadIdx.x;
+    const int row = (int)(e / (unsigned)w), x = x0 + (int)e - row * w, y = y0 + row;
+    if (row >= h || !near_support(b.box[k], x, y)) return;
+    const float* S = static_cast<const float*>(src);
+    float* D = static_cast<float*>(dst);
     float f[kQ];
-    pull_row<StF32>(static_cast<const float*>(src), g, x0 + lx, y, z, f);
-    update_cell<StF32, true, FORCE, ZH, false>(g, a.p, a, x0 + lx, y, z, f);
-    store_cell<StF32>(static_cast<float*>(dst), g, a.p, x0 + lx, y, z, f);
+    const unsigned popb = (unsigned)(g.px * sizeof(float)), slab = kQ * popb;
+    // beside a y wall or an x face, and where the region's rows pass a
+    // descriptor's 31 bits: source by source (z is periodic where there are foils)
+    if ((unsigned long long)(h + 3) * slab >= (1ull << 31) ||
+        !__all(x > 0 && x < g.nx - 1 && y > 0 && y < g.ny - 1)) {
+      pull19<StF32, true>(S, g, x, y, z, f);
+      update_cell<StF32, true, FORCE, ZH, false>(g, ph, a, x, y, z, f);
+      store_cell<StF32>(D, g, ph, x, y, z, f);
+      return;
+    }
+    // every source lies in the region's rows of three layers: one descriptor
+    // per layer (from the row before the region on), the lane's cell as its
+    // offset
+    const int zs[3] = {z == 0 ? g.nz - 1 : z - 1, z, z == g.nz - 1 ? 0 : z + 1};   // z - c_z
+    __amdgpu_buffer_rsrc_t rz[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      rz[j] = span_rsrc(reinterpret_cast<char*>(const_cast<float*>(S)) +
+                        (unsigned long long)(unsigned)(zs[j] * g.ny + y0) * slab);
+    const __amdgpu_buffer_rsrc_t rd =
+        span_rsrc(reinterpret_cast<char*>(D) + (unsigned long long)(unsigned)(z * g.ny + y0) * slab);
+    const int vo = (int)((unsigned)row * slab + (unsigned)x * 4u);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i)
+      f[i] = StF32::ldb(rz[1 - czq(i)], vo, (int)((unsigned)(1 - cyq(i)) * slab + (unsigned)i * popb) - cxq(i) * 4);
+    update_cell<StF32, true, FORCE, ZH, false>(g, ph, a, x, y, z, f);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i)
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f[i]), rd, vo, (int)(slab + (unsigned)i * popb), 0);
     return;
   }
 }
@@ -496,7 +554,7 @@ hipError_t launch_near(bool force, bool zh, const CollideArgs* const* host, cons
     for (int j = 0; j < host[k]->nw; ++j) {
       int x0, y0, w, h;
       near_region(host[k][1].box[j], host[k]->g, x0, y0, w, h);
-      waves += (long long)((w + kBlockX - 1) / kBlockX) * h * host[k]->g.nz;
+      waves += (long long)((w * h + kBlockX - 1) / kBlockX) * host[k]->g.nz;
     }
     blocks[k] = (int)((waves + kBlockRows - 1) / kBlockRows) + 1;
     g.src[k] = src[k];

@@ -100,6 +100,26 @@ def test_foil_pairs_equal_single_steps(case):
     b.close()
 
 
+@pytest.mark.parametrize("bc,centre", [([V, O, W, W, P, P], (60.2, 6.4)), ([ZV, ZO, W, W, P, P], (60.2, 184.6)),
+                                       ([P] * 6, (245.6, 11.2))], ids=["low_wall", "high_wall", "periodic"])
+def test_foil_beside_walls_pairs_equal_single_steps(bc, centre):
+    """The cells around a foil that step s is given first (k_near): beside
+    a y wall, across the periodic span, near an x face."""
+    from paper_2102_01305_amd.solver import complete_case
+
+    bx, wg, ph = WL.plate_case(nx=256, ny=192, nz=192, centre=centre)
+    u_in = [0.03, 0.0, 0.0] if bc[0] != P else [0.0, 0.0, 0.0]
+    bx, wg = complete_case(dict(bx, bc=bc, u_in=u_in), wg, ph)
+    print(f"[pair] plate at {centre} bc {bc}", flush=True)
+    a, b = _solve(bx, wg, 5), _solve(bx, wg, 5)
+    assert _updates_per_launch(a, lambda: a.step(12)) == 2.0
+    for _ in range(12):
+        b.step(1)
+    _same(a, b, ("u",))
+    a.close()
+    b.close()
+
+
 def test_batch_pairs_equal_single_steps():
     from paper_2102_01305_amd.solver import complete_case, step_batch
 
