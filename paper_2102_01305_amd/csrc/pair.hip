@@ -278,7 +278,14 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
   // in iteration q: by a wave that takes no step s+1, a lane per side and row
   // (in the waves of the rows, one lane of 64 took them a third of their time).
   auto ghosts = [&](int q) {
-    const int side = lane >> 5, row = lane & 31;
+    // With foils and a body force, what follows is made anew for each plane:
+    // kept over the loop it spilled two registers, whose reloads in the march
+    // wait for the pull in flight (clap & fling 256 x 192 x 192 with a body
+    // force 222 -> 212 us a step; the other instantiations, which do not spill,
+    // 0.5% slower by it).
+    int ln = lane;
+    if (IBM && FORCE) asm volatile("" : "+v"(ln));
+    const int side = ln >> 5, row = ln & 31;
     const int fx = side ? g.nx - 1 : 0;
     if (row < cnt && (side ? xe == g.nx : x0 == 0)) {
       float v[kQ];
