@@ -148,9 +148,9 @@ __device__ __forceinline__ void correction2(const Geo& g, const CollideArgs& a, 
 // same with R = 7 or 8 and two blocks per unit 1262-1281 us a step at
 // 512x384x384 (1228 with R = 12), R = 5 at 128 registers 1328, R = 13 1269.
 // What the march needed: descriptors per z in place of per-lane addresses, no
-// row offsets kept over the loop (168 registers and spills with them, 85-116
-// now), the next plane's pull in flight over the exchange and step s+1
-// (1427 -> 1284 us a step), and LDS by plane parity, one barrier a plane
+// row offsets kept over the loop (168 registers and spills with them, 103-128
+// now; a spilled one's reload in the march waits for the pull), the next plane's
+// pull in flight over the exchange and step s+1 (1427 -> 1284 us a step), and LDS by plane parity, one barrier a plane
 // instead of two (-> 1254).
 template <bool IBM, bool FORCE, bool ZH>
 __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, const CollideArgs& __restrict__ b,
