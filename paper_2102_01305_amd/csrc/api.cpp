@@ -843,6 +843,9 @@ int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
       return fail(h, IBMLBM_ENOMEM, "no host memory for a field transfer");
     }
   }
+  // the per-thread stream is another one in each of the threads: there the
+  // work ahead of the transfer, which is on the caller's, has to have ended
+  if (have > 1 && h->stream == hipStreamPerThread) HIP_TRY(h, hipStreamSynchronize(h->stream));
   std::atomic<size_t> next{0};
   std::atomic<int> err{hipSuccess};
   auto work = [&](int t) {

@@ -1,0 +1,39 @@
+"""The host side of the C ABI on a CPU (host_runtime.cpp stands in for the HIP
+runtime and the kernels): which stream, thread and device its work is put on,
+and what a call leaves behind."""
+import ctypes as C
+import threading
+
+import numpy as np
+import pytest
+
+import host_runtime as H
+import workloads as WL
+from paper_2102_01305_amd import _lib as L
+
+P = WL.PERIODIC
+W = np.array([1 / 3] + [1 / 18] * 6 + [1 / 36] * 12)[:, None, None, None]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return H.build(tmp_path_factory.mktemp("host_side"))
+
+
+def _transfers(s):
+    """Fields of a few chunks up and down, checked value by value."""
+    n = int(np.prod(s.shape))
+    f = W + np.random.default_rng(n).uniform(-2e-2, 2e-2, (19,) + s.shape)
+    s.init(fdist=f)
+    np.testing.assert_array_equal(s.fields(L.FIELD_FDIST), W + (f - W).astype(np.float32).astype(np.float64))
+    want = (np.arange(4 * n) % 65521).astype(np.float64)
+    np.testing.assert_array_equal(s.fields(L.FIELD_RHO).reshape(-1), want[:n])
+    np.testing.assert_array_equal(s.fields(L.FIELD_U).reshape(-1), want[n:])
+
+
+@pytest.mark.parametrize("stream", ["null", "own", "per_thread"])
+def test_transfers_come_after_the_kernels_of_any_kind_of_stream(lib, stream):
+    st = {"null": None, "own": lib.host_stream(0), "per_thread": H.PER_THREAD}[stream]
+    s = H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6), stream=st)   # 2.4 MB a population: 23 chunks
+    _transfers(s)
+    s.close()
