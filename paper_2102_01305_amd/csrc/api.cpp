@@ -108,6 +108,7 @@ struct ibmlbm_s {
   // with the first such transfer, given back with the handle)
   void* slot[kSlots] = {};
   hipEvent_t slot_ev[kSlots] = {};
+  int slot_dev[kSlots] = {};        // device of the slot's event
   int slots = 0;
   // timing
   bool timing = false;
@@ -805,22 +806,48 @@ int fill_window(ibmlbm_t h, long long s0) {
   return IBMLBM_OK;
 }
 
-// Pinned slots for up to n threads; how many there are (0 for handles that
-// must not allocate, or where there is no pinned memory left).
-int ensure_slots(ibmlbm_t h, int n) {
-  while (!h->noalloc && h->slots < n) {
-    void* p = nullptr;
-    hipEvent_t ev = nullptr;
-    if (hipHostMalloc(&p, kSlotBytes, hipHostMallocDefault) != hipSuccess ||
-        hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+// Makes the device of h's stream, which need not be the caller's current one,
+// current until the end of the scope: events belong to a device, and so do the
+// host threads of a field transfer.
+struct DeviceScope {
+  int before = -1;
+  hipError_t enter(ibmlbm_t h) {
+    if (h->stream == nullptr || h->stream == hipStreamLegacy || h->stream == hipStreamPerThread)
+      return hipSuccess;                               // (these are the current device's)
+    int now = 0, device = 0;
+    hipError_t e = hipGetDevice(&now);
+    if (e == hipSuccess) e = hipStreamGetDevice(h->stream, &device);
+    if (e != hipSuccess || now == device) return e;
+    before = now;
+    return hipSetDevice(device);
+  }
+  ~DeviceScope() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
+// Pinned slots for up to n threads, with events of the current device, which
+// is `device`; how many there are (0 for handles that must not allocate, or
+// where there is no pinned memory left).
+int ensure_slots(ibmlbm_t h, int n, int device) {
+  int have = 0;
+  for (; have < n && !h->noalloc; ++have) {
+    void*& p = h->slot[have];
+    hipEvent_t& ev = h->slot_ev[have];
+    if (ev && h->slot_dev[have] != device) {
+      (void)hipEventDestroy(ev);
+      ev = nullptr;
+    }
+    if (!p && hipHostMalloc(&p, kSlotBytes, hipHostMallocDefault) != hipSuccess) p = nullptr;
+    h->slots = std::max(h->slots, p ? have + 1 : have);
+    if (p && !ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
+    h->slot_dev[have] = device;
+    if (!p || !ev) {
       (void)hipGetLastError();
-      if (p) (void)hipHostFree(p);
       break;
     }
-    h->slot[h->slots] = p;
-    h->slot_ev[h->slots++] = ev;
   }
-  return std::min(n, h->slots);
+  return have;
 }
 
 // Move n floats between `dev` and the host on h's stream, chunk by chunk:
@@ -831,10 +858,10 @@ int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
   const size_t chunk = kSlotBytes / sizeof(float), chunks = (n + chunk - 1) / chunk;
   if (n == 0) return IBMLBM_OK;
   const unsigned cores = std::max(1u, std::thread::hardware_concurrency());
-  int device = 0;
+  int device = 0;                                      // (of the stream: the entry points make it current)
   HIP_TRY(h, hipGetDevice(&device));
   const int want = (int)std::min<size_t>({chunks, (size_t)kSlots, (size_t)cores});
-  const int have = ensure_slots(h, want);
+  const int have = ensure_slots(h, want, device);
   std::vector<float> plain;                            // staging where there is no pinned memory
   if (have == 0) {
     try {
@@ -1220,6 +1247,8 @@ int ibmlbm_create_noalloc(const ibmlbm_config* cfg, void* dev_state, size_t byte
 int ibmlbm_init_fields(ibmlbm_t h, const double* rho, const double* u, const double* fdist, int64_t step0) {
   if (!h) return fail(nullptr, IBMLBM_EINVAL, "null handle");
   if (step0 < 0) return fail(h, IBMLBM_EINVAL, "step0 must be >= 0");
+  DeviceScope scope;
+  HIP_TRY(h, scope.enter(h));
   const LatticeLayout& L = h->L;
   const size_t N = L.N;
   h->cur_is_A = true;
@@ -1402,6 +1431,8 @@ int ibmlbm_fields(ibmlbm_t h, int32_t which, double* out) {
   if (!h) return fail(nullptr, IBMLBM_EINVAL, "null handle");
   if (!out) return fail(h, IBMLBM_EINVAL, "null output");
   if (!h->initialized) return fail(h, IBMLBM_ESTATE, "fields before init_fields");
+  DeviceScope scope;
+  HIP_TRY(h, scope.enter(h));
   const LatticeLayout& L = h->L;
   const size_t N = L.N;
   if (which == IBMLBM_FIELD_RHO || which == IBMLBM_FIELD_U) {
@@ -1519,7 +1550,7 @@ int ibmlbm_destroy(ibmlbm_t h) {
   if (h->pin_ev) (void)hipEventDestroy(h->pin_ev);
   if (h->pin) (void)hipHostFree(h->pin);
   for (int t = 0; t < h->slots; ++t) {
-    (void)hipEventDestroy(h->slot_ev[t]);
+    if (h->slot_ev[t]) (void)hipEventDestroy(h->slot_ev[t]);
     (void)hipHostFree(h->slot[t]);
   }
   delete h;

@@ -71,6 +71,7 @@ void enqueue(hipStream_t st, std::function<void()> f) {
 // Enqueue a launch of the named kind, or fail as asked for by host_fail.
 hipError_t launch(const std::string& kind, const std::string& what, hipStream_t st, std::function<void()> f) {
   std::lock_guard<std::recursive_mutex> l(mu);
+  if (find(st)->device != current) return hipErrorInvalidDevice;
   if (kind == fail_kind && fail_after-- == 0) return fail_kind.clear(), hipErrorLaunchFailure;
   calls.push_back(what);
   enqueue(st, std::move(f));

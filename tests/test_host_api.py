@@ -37,3 +37,20 @@ def test_transfers_come_after_the_kernels_of_any_kind_of_stream(lib, stream):
     s = H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6), stream=st)   # 2.4 MB a population: 23 chunks
     _transfers(s)
     s.close()
+
+
+def test_transfers_with_another_device_current(lib):
+    """A solve made on one device is read and written with another current,
+    and the current device stays what it was."""
+    lib.host_device(1)
+    s = H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6), stream=lib.host_stream(1))
+    for current in (0, 1, 0):
+        lib.host_device(current)
+        _transfers(s)
+        assert lib.host_current() == current
+    # and on a stream of the other device from then on
+    s.check(lib.ibmlbm_set_stream(s.h, C.c_void_p(lib.host_stream(0))))
+    lib.host_device(1)
+    _transfers(s)
+    lib.host_device(0)
+    s.close()
