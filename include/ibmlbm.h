@@ -22,10 +22,11 @@
  *  - Device memory is owned by the caller: one workspace of at least
  *    ibmlbm_workspace_bytes() bytes, 256-byte aligned, handed to create().
  *    The library never allocates device memory.  The library owns only the
- *    host-side handle and, per handle, pinned host memory: a small buffer
+ *    host-side handle and pinned host memory: per handle a small buffer
  *    (about 210 KB) through which it uploads the launch arguments of 64 steps
- *    at a time and returns force rows, and, from the first call that moves a
- *    whole field on, up to 16 MB of staging, given back by destroy.  Input
+ *    at a time and returns force rows, and, for the calls that move a whole
+ *    field, staging that all handles of the process share (16 MB for one such
+ *    call at a time, at most 64 MB), given back with the last handle.  Input
  *    arrays are copied, never retained.
  *  - Work is enqueued on the caller's HIP stream (hipStream_t passed as
  *    void*; NULL = the null stream).  step() only enqueues; forces(),

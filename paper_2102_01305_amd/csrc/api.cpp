@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -64,6 +65,88 @@ constexpr int kPwStride = 14;      // doubles per perimeter record (markers.hip)
 // 17 GB/s, eight at 60.
 constexpr int kSlots = 8;
 constexpr size_t kSlotBytes = size_t(2) << 20;
+constexpr int kPoolSlots = 32;     // of all handles together: four transfers at once
+
+// Pinned staging of one thread of a transfer, with an event of one device.
+struct Slot {
+  void* buf = nullptr;
+  hipEvent_t ev = nullptr;
+  int device = -1;
+};
+
+// The slots of the process.  Transfers of any handles borrow them, from any
+// threads; they are made as transfers need them and given back with the last
+// handle (a handle of its own eight each pinned 1 GB for 64 resident solves).
+class SlotPool {
+ public:
+  // Up to n slots with events of the current device, which is `device`; how
+  // many there are (0: all in use, or no pinned memory left).
+  int borrow(Slot* out, int n, int device) {
+    int have = 0;
+    while (have < n && take(out[have])) {
+      Slot& s = out[have];
+      if (s.ev && s.device != device) {
+        (void)hipEventDestroy(s.ev);
+        s.ev = nullptr;
+      }
+      s.device = device;
+      if (!s.buf && hipHostMalloc(&s.buf, kSlotBytes, hipHostMallocPortable) != hipSuccess) s.buf = nullptr;
+      if (s.buf && !s.ev && hipEventCreateWithFlags(&s.ev, hipEventDisableTiming) != hipSuccess) s.ev = nullptr;
+      if (!s.ev) {
+        (void)hipGetLastError();
+        if (s.buf) (void)hipHostFree(s.buf);
+        std::lock_guard<std::mutex> lock(mu_);
+        --made_;
+        break;
+      }
+      ++have;
+    }
+    return have;
+  }
+  void give_back(const Slot* s, int n) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (int k = 0; k < n; ++k) slot_[free_++] = s[k];
+  }
+  void handle_made() {
+    std::lock_guard<std::mutex> lock(mu_);
+    ++handles_;
+  }
+  // (no transfer is under way when the last handle goes)
+  void handle_gone() {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (--handles_ > 0) return;
+    made_ -= free_;
+    while (free_ > 0) {
+      const Slot& s = slot_[--free_];
+      (void)hipEventDestroy(s.ev);
+      (void)hipHostFree(s.buf);
+    }
+  }
+
+ private:
+  // a free slot, or an empty one where there may be more
+  bool take(Slot& s) {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (free_ > 0)
+      s = slot_[--free_];
+    else if (made_ < kPoolSlots)
+      s = Slot{}, ++made_;
+    else
+      return false;
+    return true;
+  }
+
+  std::mutex mu_;
+  Slot slot_[kPoolSlots];            // those not borrowed
+  int free_ = 0, made_ = 0;
+  long long handles_ = 0;
+};
+
+// (never destroyed: threads of the caller may outlive static objects)
+SlotPool& slot_pool() {
+  static SlotPool* p = new SlotPool;
+  return *p;
+}
 
 struct MarkerLayout {
   Region ref, G, Minv, pw, sup, T, X, U, B, rhoB, duB, fpart, hist;
@@ -104,12 +187,7 @@ struct ibmlbm_s {
   void* pin = nullptr;              // pinned staging of the window upload, then of force rows
   hipEvent_t pin_ev = nullptr;      // completes when the last upload has been read
   bool pin_pending = false;
-  // pinned staging of field transfers, a slot per thread that moves them (made
-  // with the first such transfer, given back with the handle)
-  void* slot[kSlots] = {};
-  hipEvent_t slot_ev[kSlots] = {};
-  int slot_dev[kSlots] = {};        // device of the slot's event
-  int slots = 0;
+  bool pooled = false;              // counted among the handles of the slot pool
   // timing
   bool timing = false;
   int timing_every = 1;             // bracket one step in this many
@@ -826,30 +904,6 @@ struct DeviceScope {
   }
 };
 
-// Pinned slots for up to n threads, with events of the current device, which
-// is `device`; how many there are (0 for handles that must not allocate, or
-// where there is no pinned memory left).
-int ensure_slots(ibmlbm_t h, int n, int device) {
-  int have = 0;
-  for (; have < n && !h->noalloc; ++have) {
-    void*& p = h->slot[have];
-    hipEvent_t& ev = h->slot_ev[have];
-    if (ev && h->slot_dev[have] != device) {
-      (void)hipEventDestroy(ev);
-      ev = nullptr;
-    }
-    if (!p && hipHostMalloc(&p, kSlotBytes, hipHostMallocDefault) != hipSuccess) p = nullptr;
-    h->slots = std::max(h->slots, p ? have + 1 : have);
-    if (p && !ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
-    h->slot_dev[have] = device;
-    if (!p || !ev) {
-      (void)hipGetLastError();
-      break;
-    }
-  }
-  return have;
-}
-
 // Move n floats between `dev` and the host on h's stream, chunk by chunk:
 // fn(begin, count, buf) fills buf before its upload (up) or takes it after its
 // download.  Returns when all are moved.
@@ -861,7 +915,14 @@ int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
   int device = 0;                                      // (of the stream: the entry points make it current)
   HIP_TRY(h, hipGetDevice(&device));
   const int want = (int)std::min<size_t>({chunks, (size_t)kSlots, (size_t)cores});
-  const int have = ensure_slots(h, want, device);
+  struct Borrowed {
+    Slot slot[kSlots];
+    int n = 0;
+    ~Borrowed() { slot_pool().give_back(slot, n); }
+  } borrowed;
+  Slot* const slot = borrowed.slot;
+  if (!h->noalloc) borrowed.n = slot_pool().borrow(slot, want, device);
+  const int have = borrowed.n;
   std::vector<float> plain;                            // staging where there is no pinned memory
   if (have == 0) {
     try {
@@ -877,7 +938,7 @@ int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
   std::atomic<int> err{hipSuccess};
   auto work = [&](int t) {
     if (t > 0 && hipSetDevice(device) != hipSuccess) return;
-    float* buf = have == 0 ? plain.data() : static_cast<float*>(h->slot[t]);
+    float* buf = have == 0 ? plain.data() : static_cast<float*>(slot[t].buf);
     for (size_t c; err.load() == hipSuccess && (c = next.fetch_add(1)) < chunks;) {
       const size_t begin = c * chunk, count = std::min(chunk, n - begin);
       if (up) fn(begin, count, buf);
@@ -888,8 +949,8 @@ int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
       if (have == 0) {
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
       } else {
-        if (e == hipSuccess) e = hipEventRecord(h->slot_ev[t], h->stream);
-        if (e == hipSuccess) e = hipEventSynchronize(h->slot_ev[t]);
+        if (e == hipSuccess) e = hipEventRecord(slot[t].ev, h->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(slot[t].ev);
       }
       if (e != hipSuccess)
         err.store(e);
@@ -907,6 +968,7 @@ int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
   for (auto& t : hands)
     if (t.joinable()) t.join();
   const hipError_t e = (hipError_t)err.load();
+  if (e != hipSuccess) (void)hipStreamSynchronize(h->stream);   // (a copy may still use a slot)
   if (e != hipSuccess) return fail(h, IBMLBM_EDEVICE, "field transfer failed: %s", hipGetErrorString(e));
   return IBMLBM_OK;
 }
@@ -1214,6 +1276,10 @@ int create_handle(const ibmlbm_config* cfg, void* dev_buf, size_t bytes, void* h
     int r = fail(nullptr, IBMLBM_EDEVICE, "create failed: %s", hipGetErrorString(e));
     ibmlbm_destroy(h);
     return r;
+  }
+  if (!noalloc) {
+    slot_pool().handle_made();
+    h->pooled = true;
   }
   *out = h;
   return IBMLBM_OK;
@@ -1549,10 +1615,7 @@ int ibmlbm_destroy(ibmlbm_t h) {
   for (auto& ev : h->ev) (void)hipEventDestroy(ev);
   if (h->pin_ev) (void)hipEventDestroy(h->pin_ev);
   if (h->pin) (void)hipHostFree(h->pin);
-  for (int t = 0; t < h->slots; ++t) {
-    if (h->slot_ev[t]) (void)hipEventDestroy(h->slot_ev[t]);
-    (void)hipHostFree(h->slot[t]);
-  }
+  if (h->pooled) slot_pool().handle_gone();
   delete h;
   if (e != hipSuccess) return fail(nullptr, IBMLBM_EDEVICE, "stream error at destroy: %s", hipGetErrorString(e));
   return IBMLBM_OK;

@@ -54,3 +54,30 @@ def test_transfers_with_another_device_current(lib):
     _transfers(s)
     lib.host_device(0)
     s.close()
+
+
+def test_pinned_staging_is_bounded_for_all_solves_and_given_back(lib):
+    assert lib.host_pinned(0) == 0
+    made = [H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6), stream=lib.host_stream(0)) for _ in range(8)]
+    handles = lib.host_pinned(0)                       # what each handle holds for its launch arguments
+    for s in made[:3]:
+        _transfers(s)
+    assert lib.host_pinned(0) - handles <= 16 << 20    # one after the other: the staging of one transfer
+    errors = []
+
+    def go(s):
+        try:
+            _transfers(s)
+        except AssertionError as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=go, args=(s,)) for s in made]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    assert lib.host_pinned(1) - handles <= 64 << 20    # however many at once
+    for s in made:
+        s.close()
+    assert lib.host_pinned(0) == 0
