@@ -1093,6 +1093,21 @@ int run_steps(ibmlbm_t* hs, int n, int steps) {
   enum Mode : char { SINGLE, FIRST, SECOND };
   Mode mode[kMaxGroup];
   int planes[kMaxGroup];
+  // On an error a solve between the two steps of a pair goes back to the step
+  // of the state it still has, and every solve starts its next window anew
+  // (the one at hand may be half made): the call can be made again.
+  struct Undo {
+    ibmlbm_t* hs;
+    int n;
+    bool half[kMaxGroup] = {}, done = false;
+    ~Undo() {
+      for (int j = 0; j < n && !done; ++j) {
+        hs[j]->step -= half[j];
+        hs[j]->win_t0 = -1;
+        hs[j]->ev_used &= ~size_t(1);                  // (a timing bracket left open)
+      }
+    }
+  } undo{hs, n};
   for (int j = 0; j < n; ++j) mode[j] = SINGLE;
   plan_pairs(hs, n, steps, planes);
   std::vector<const MarkerArgs*> mh;
@@ -1209,11 +1224,13 @@ int run_steps(ibmlbm_t* hs, int n, int steps) {
         HIP_TRY(h, launch_mass_reduce(at<double>(h, h->L.mass_part), h->L.nblocks,
                                       (double)h->L.N,
                                       reinterpret_cast<double*>(h->sb + h->L.diag.off), s + 1, st));
-      if (mode[j] != FIRST) h->cur_is_A = !h->cur_is_A;
+      undo.half[j] = mode[j] == FIRST;
+      if (!undo.half[j]) h->cur_is_A = !h->cur_is_A;
       h->step = s + 1;
       if (h->nw > 0) h->markers_valid = true;
     }
   }
+  undo.done = true;
   return IBMLBM_OK;
 }
 

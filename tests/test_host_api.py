@@ -81,3 +81,38 @@ def test_pinned_staging_is_bounded_for_all_solves_and_given_back(lib):
     for s in made:
         s.close()
     assert lib.host_pinned(0) == 0
+
+
+def _foil_solve(lib, nx=256, ny=192, nz=192, chord=20.0, step0=0, **kw):
+    import oracle.params as params
+
+    bx, wg, ph = WL.clap_fling_case(nx=nx, ny=ny, nz=nz, chord=chord)
+    bx, wg = params.complete_case(bx, wg, ph)
+    s = H.Solve(lib, bx, wg, **kw)
+    s.init(step0=step0)
+    return s
+
+
+def _steps_done(s):
+    """Steps that the solve's current state has seen: the further of the two
+    states (the idle one is older, or was written by a step not yet taken)."""
+    s.check(s.lib.ibmlbm_mass(s.h, C.byref(C.c_int64()), C.byref(C.c_double())))   # (waits for the stream)
+    return max(int(v[0]) for v in s.state)
+
+
+@pytest.mark.parametrize("kind,after", [("factor", 0), ("markers", 0), ("near", 0), ("markers", 1), ("pair", 0),
+                                        ("markers", 3), ("pair", 1)])
+def test_an_error_between_the_steps_of_a_pair_loses_no_step(lib, kind, after):
+    """The step count stays that of the state the solve still has, and the
+    next call goes on from there."""
+    s = _foil_solve(lib)
+    lib.host_calls()
+    lib.host_fail(kind.encode(), after)
+    assert lib.ibmlbm_step(s.h, 10) == L.EDEVICE
+    assert s.step_count() == _steps_done(s)
+    lib.host_calls()
+    s.check(lib.ibmlbm_step(s.h, 70 - s.step_count()))
+    calls = lib.host_calls().decode().split()
+    assert calls[0] == "factor" and "pair" in calls    # (the failed window is made again)
+    assert s.step_count() == _steps_done(s) == 70
+    s.close()
