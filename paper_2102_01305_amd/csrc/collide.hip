@@ -292,16 +292,17 @@ __global__ void k_dense(Geo g, float* dense, int q0, int nq, typename St::T* sta
   }
 }
 
+// (hipLaunchKernel returns the launch's own status: hipGetLastError would also
+// give an error that some earlier call of the thread left, and the read-backs
+// are answered whatever that was)
 template <bool PACK>
-static hipError_t launch_dense(int storage, const Geo& g, float* dense, int q0, int nq, void* state, hipStream_t s) {
+static hipError_t launch_dense(int storage, Geo g, float* dense, int q0, int nq, void* state, hipStream_t s) {
   const size_t N = (size_t)g.nx * g.ny * g.nz;
-  const unsigned nb = (unsigned)((N + 255) / 256);
-  switch (storage) {
-    case ST_F32: k_dense<StF32, PACK><<<nb, 256, 0, s>>>(g, dense, q0, nq, static_cast<float*>(state)); break;
-    case ST_F16: k_dense<StF16, PACK><<<nb, 256, 0, s>>>(g, dense, q0, nq, static_cast<__half*>(state)); break;
-    default: k_dense<StBF16, PACK><<<nb, 256, 0, s>>>(g, dense, q0, nq, static_cast<unsigned short*>(state)); break;
-  }
-  return hipGetLastError();
+  void* args[] = {&g, &dense, &q0, &nq, &state};
+  const void* fn = storage == ST_F32   ? reinterpret_cast<const void*>(k_dense<StF32, PACK>)
+                   : storage == ST_F16 ? reinterpret_cast<const void*>(k_dense<StF16, PACK>)
+                                       : reinterpret_cast<const void*>(k_dense<StBF16, PACK>);
+  return hipLaunchKernel(fn, dim3((unsigned)((N + 255) / 256)), dim3(256), args, 0, s);
 }
 
 hipError_t launch_pack(int storage, const Geo& g, const float* dense, int q0, int nq, void* state, hipStream_t s) {
@@ -321,8 +322,8 @@ __global__ void k_export(const double* hist, long long first, long long ring, in
 
 hipError_t launch_export(const double* hist, long long first, long long ring, int n, int row, const int* flags,
                          double* out, hipStream_t s) {
-  k_export<<<1, 256, 0, s>>>(hist, first, ring, n, row, flags, out);
-  return hipGetLastError();
+  void* args[] = {&hist, &first, &ring, &n, &row, &flags, &out};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k_export), dim3(1), dim3(256), args, 0, s);
 }
 
 __global__ void k_mass_reduce(const double* part, int n, double ncells, double* out, long long step) {

@@ -69,3 +69,25 @@ def test_force_rows_by_kernel_and_by_copies(history):
     one = np.concatenate([s.forces(first + k, 1) for k in range(all_rows.shape[0])])
     np.testing.assert_array_equal(one, all_rows)
     s.close()
+
+
+def test_read_back_does_not_answer_for_errors_of_other_calls():
+    """An error that some other call of the thread left behind is not a failure
+    of force rows or checkpoints."""
+    import ctypes
+
+    import torch  # noqa: F401  (maps the HIP runtime)
+
+    print("[transfer] after another call's error", flush=True)
+    bx, wg, ph, u0 = plate(seed=5, nz=8)
+    s = gpu_solver(bx, wg, ph, u0=u0)
+    s.step(3)
+    f, d = s.forces(0, 3), s.fields("fdist")
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)                            # (the one already mapped)
+    assert hip.hipSetDevice(1 << 20) != 0              # no such device: an error of the runtime, nothing runs
+    np.testing.assert_array_equal(s.forces(0, 3), f)
+    assert hip.hipSetDevice(1 << 20) != 0
+    np.testing.assert_array_equal(s.fields("fdist"), d)
+    hip.hipGetLastError()
+    s.close()
