@@ -249,62 +249,6 @@ inline int group_fill(Group& g, const void* const* dev, const int* blocks, int n
   return t;
 }
 
-// Zou-He faces: rebuild the populations entering through an x face at a
-// boundary cell from its known ones (non-equilibrium bounce-back of the
-// normal population plus a transverse momentum correction, D3Q19), so that
-// the cell carries the prescribed velocity (density from the known
-// populations) or the prescribed density (transverse velocity zero).
-// Cells whose entering links also touch a y or z wall keep the ghost values
-// pulled already.  f holds deviations f - w, times s (stored units) if RAW;
-// the lattice weights cancel in every difference used here.
-template <class St, bool RAW, int IN>
-__device__ __forceinline__ void zou_he_face(const Phys& p, int kind, float f[kQ]) {
-  // IN: c_x of the entering populations (+1 on the -x face, -1 on the +x face)
-  const float s = RAW ? St::kS : 1.0f, inv = RAW ? St::kInv : 1.0f;
-  float sz = 0.f, sout = 0.f, ny = 0.f, nz = 0.f;  // sums over c_x = 0 and leaving populations
-#pragma unroll
-  for (int i = 0; i < kQ; ++i) {
-    if (cxq(i) == 0) {
-      sz += f[i];
-      ny += cyq(i) * f[i];
-      nz += czq(i) * f[i];
-    } else if (cxq(i) == -IN) {
-      sout += f[i];
-    }
-  }
-  const float known = 1.0f + (sz + 2.0f * sout) * inv;   // sum_Z f + 2 sum_out f
-  float rho, ux, uy, uz;
-  if (kind == BC_ZH_VELOCITY) {
-    ux = p.u_in[0]; uy = p.u_in[1]; uz = p.u_in[2];
-    rho = known / (1.0f - IN * ux);
-  } else {
-    rho = p.rho_out;
-    ux = IN * (1.0f - known / rho);
-    uy = 0.f; uz = 0.f;
-  }
-  const float Ny = 0.5f * ny - s * rho * uy * (1.0f / 3.0f);
-  const float Nz = 0.5f * nz - s * rho * uz * (1.0f / 3.0f);
-#pragma unroll
-  for (int i = 0; i < kQ; ++i) {
-    if (cxq(i) != IN) continue;
-    const float cu = cxq(i) * ux + cyq(i) * uy + czq(i) * uz;
-    f[i] = f[oppq(i)] + s * 6.0f * wq(i) * rho * cu - cyq(i) * Ny - czq(i) * Nz;
-  }
-}
-
-template <class St, bool RAW>
-__device__ __forceinline__ void zou_he(const Geo& g, const Phys& p, int x, int y, int z, float f[kQ]) {
-  const bool lo = x == 0 && g.bclo >= BC_ZH_VELOCITY;
-  const bool hi = x == g.nx - 1 && g.bchi >= BC_ZH_VELOCITY;
-  if (!lo && !hi) return;
-  if (!g.yper && (y == 0 || y == g.ny - 1)) return;
-  if (!g.zper && (z == 0 || z == g.nz - 1)) return;
-  if (lo)
-    zou_he_face<St, RAW, 1>(p, g.bclo, f);
-  else
-    zou_he_face<St, RAW, -1>(p, g.bchi, f);
-}
-
 // c_i . v summed over the nonzero components of c_i in x, y, z order.  A
 // product 0 * v is not folded away under IEEE rules (v could be infinite),
 // and leaving it out changes no finite result.
@@ -321,6 +265,68 @@ __device__ __forceinline__ float cdot(int i, float vx, float vy, float vz) {
     any = true;
   }
   return r;
+}
+
+// Zou-He faces: rebuild the populations entering through an x face at a
+// boundary cell from its known ones (non-equilibrium bounce-back of the
+// normal population plus a transverse momentum correction, D3Q19), so that
+// the cell carries the prescribed velocity (density from the known
+// populations) or the prescribed density (transverse velocity zero).
+// Cells whose entering links also touch a y or z wall keep the ghost values
+// pulled already.  f holds deviations f - w, times s (stored units) if RAW;
+// the lattice weights cancel in every difference used here.
+// Every operation and fused multiply-add is written out, as in the cell update
+// it is part of: the same bits in whatever kernel it is compiled into (left to
+// the compiler, which of two products is rounded can differ between kernels).
+template <class St, bool RAW, int IN>
+__device__ __forceinline__ void zou_he_face(const Phys& p, int kind, float f[kQ]) {
+#pragma clang fp contract(off)
+  // IN: c_x of the entering populations (+1 on the -x face, -1 on the +x face)
+  const float s = RAW ? St::kS : 1.0f, inv = RAW ? St::kInv : 1.0f;
+  float sz = 0.f, sout = 0.f, ny = 0.f, nz = 0.f;  // sums over c_x = 0 and leaving populations
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) {
+    if (cxq(i) == 0) {
+      sz += f[i];
+      if (cyq(i) != 0) ny = cyq(i) > 0 ? ny + f[i] : ny - f[i];
+      if (czq(i) != 0) nz = czq(i) > 0 ? nz + f[i] : nz - f[i];
+    } else if (cxq(i) == -IN) {
+      sout += f[i];
+    }
+  }
+  const float known = __builtin_fmaf(__builtin_fmaf(2.0f, sout, sz), inv, 1.0f);   // sum_Z f + 2 sum_out f
+  float rho, ux, uy, uz;
+  if (kind == BC_ZH_VELOCITY) {
+    ux = p.u_in[0]; uy = p.u_in[1]; uz = p.u_in[2];
+    rho = known / (1.0f - IN * ux);
+  } else {
+    rho = p.rho_out;
+    ux = IN * (1.0f - known / rho);
+    uy = 0.f; uz = 0.f;
+  }
+  const float Ny = __builtin_fmaf(0.5f, ny, -(s * rho * uy * (1.0f / 3.0f)));
+  const float Nz = __builtin_fmaf(0.5f, nz, -(s * rho * uz * (1.0f / 3.0f)));
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) {
+    if (cxq(i) != IN) continue;
+    float v = __builtin_fmaf(s * 6.0f * wq(i) * rho, cdot(i, ux, uy, uz), f[oppq(i)]);
+    if (cyq(i) != 0) v = cyq(i) > 0 ? v - Ny : v + Ny;
+    if (czq(i) != 0) v = czq(i) > 0 ? v - Nz : v + Nz;
+    f[i] = v;
+  }
+}
+
+template <class St, bool RAW>
+__device__ __forceinline__ void zou_he(const Geo& g, const Phys& p, int x, int y, int z, float f[kQ]) {
+  const bool lo = x == 0 && g.bclo >= BC_ZH_VELOCITY;
+  const bool hi = x == g.nx - 1 && g.bchi >= BC_ZH_VELOCITY;
+  if (!lo && !hi) return;
+  if (!g.yper && (y == 0 || y == g.ny - 1)) return;
+  if (!g.zper && (z == 0 || z == g.nz - 1)) return;
+  if (lo)
+    zou_he_face<St, RAW, 1>(p, g.bclo, f);
+  else
+    zou_he_face<St, RAW, -1>(p, g.bchi, f);
 }
 
 // Zeroth and first moments of 19 values: sum f_i and sum c_i f_i, in i order
