@@ -10,6 +10,7 @@
 //            each layer (Eq. 26) and sum_l du_B D dA over the layer (Eq. 15).
 #include "lattice_dev.h"
 #include "kinematics.h"
+#include "span_lds.h"
 
 namespace ibmk {
 
@@ -307,46 +308,11 @@ __device__ __forceinline__ int find_layer_block(const MarkerArgs& a, int blk, in
 //    s2 range; the parts are added in a fixed order.  T is written
 //    layer-major.
 // One block holds every layer of its marker, so B never leaves the block.
-__host__ __device__ inline int parts_at(int ns, int threads) {
-  const int groups = (ns + 3) / 4;                   // threads per part
-  const int parts = threads / groups;
-  return parts < 1 ? 1 : (parts > 8 ? 8 : parts);
-}
-
-// Longest span whose interpolation blocks pull the moments of their marker's
-// 16 nodes a layer themselves, with no band launch before them: a launch of
-// the smallest chain is 4 us of latency.  Neighbouring markers then pull most
-// nodes again, so it pays while half a block's threads take them in one turn.
-// Step of clap & fling in us, band launch / pulled: 64x48x8 27.3 / 24.0,
-// 96x80x16 28.9 / 27.5, 96x80x32 32.1 / 34.4, 96x80x48 36.0 / 41.3; 2D figure
-// eight 1000x500 38.7 / 35.3.
-constexpr int kPullSpan = 16;
-
-// LDS of a block: G (2 ns), B (3 ns), partial sums (parts x 3 ns), the
-// xy sums R (4 ns) and, where it pulls them, the nodes' moments (32 ns).
-__host__ __device__ inline size_t interp_span_doubles(int ns, int parts) {
-  const size_t d = (size_t)(9 + 3 * parts + (ns <= kPullSpan ? 32 : 0)) * ns;
-  return (d + 1) / 2 * 2;
-}
-__host__ __device__ inline size_t lds_at(int ns, int threads) {
-  return interp_span_doubles(ns, parts_at(ns, threads)) * sizeof(double);
-}
-
-// Threads of an interp_span block for a span of ns layers: 512 (more parts
-// of the span range in parallel) where its LDS fits, else 256.
-__host__ __device__ inline int span_threads(int ns) { return lds_at(ns, 512) <= 150 * 1024 ? 512 : 256; }
-
-// Parts of the span range and LDS of a block: fixed by ns alone, so a
-// solve sums its span solve in the same order whatever block size a grouped
-// launch runs it with (a smaller block takes the parts in turns).
-__host__ __device__ inline int span_parts(int ns) { return parts_at(ns, span_threads(ns)); }
-__host__ __device__ inline size_t interp_span_lds(int ns) { return lds_at(ns, span_threads(ns)); }
-
 // PULL: solves with spans up to kPullSpan are among the launch (without the
 // pull the kernel takes fewer registers: chain -0.6 us at 96x80x80).
 template <class St, bool PULL>
 __device__ __forceinline__ void interp_span_block(const MarkerArgs& __restrict__ a, int lb, const void* src) {
-  extern __shared__ double lds[];
+  extern __shared__ __attribute__((aligned(16))) double lds[];
   // workgroups are dealt to the 8 XCDs in turn: blocks lb = 8 k + x take
   // the run of markers x * (M / 8) + k, so neighbouring markers, which
   // share most of their band records, read them through one L2 (a
@@ -391,7 +357,7 @@ __device__ __forceinline__ void interp_span_block(const MarkerArgs& __restrict__
     typedef float v4f __attribute__((ext_vector_type(4)));   // one 16-byte load per record
     const auto* band = gmem(reinterpret_cast<const v4f*>(w.band));
     const bool pull = PULL && ns <= kPullSpan;
-    float4* nodes = reinterpret_cast<float4*>(R + 4 * ns);   // 16 per layer
+    float4* nodes = reinterpret_cast<float4*>(lds + nodes_at(ns, parts));   // 16 per layer
     if (pull) {
       for (int e = threadIdx.x; e < 16 * ns; e += bd)
         nodes[e] = node_moments<St>(a, src, (int)r[12] + (e & 3), (int)r[13] + ((e >> 2) & 3), e >> 4);
