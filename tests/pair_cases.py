@@ -1,0 +1,17 @@
+"""Solves whose steps are taken in pairs (two in one pass over the lattice), for
+the GPU tests that compare pairs with single steps and for the CPU test that
+checks that they are planned so."""
+import workloads as WL
+
+P, W, V, O, ZV, ZO = (WL.PERIODIC, WL.WALL, WL.VELOCITY, WL.PRESSURE, WL.ZH_VELOCITY, WL.ZH_PRESSURE)
+
+FACES = {"periodic": [P] * 6, "channel": [V, O, W, W, P, P], "closed": [W] * 6, "zou_he": [ZV, ZO, W, W, P, P],
+         "zou_he_z_walls": [ZO, ZV, P, P, W, W], "duct": [P, P, W, W, W, W], "wall_out": [W, O, P, P, P, P]}
+
+# a last column of one cell (129, 257) and a box narrower than a column (61),
+# each with a last tile of one row along z (12 k + 1)
+RAGGED = [(129, 97, 133), (257, 97, 49), (61, 200, 205)]
+
+
+def lattice(size, bc):
+    return WL.box(*size, bc, 0.6, u_in=(0.03, 0.002, -0.001) if bc[0] != P else (0, 0, 0), rho_out=1.001)

@@ -116,3 +116,22 @@ def test_an_error_between_the_steps_of_a_pair_loses_no_step(lib, kind, after):
     assert calls[0] == "factor" and "pair" in calls    # (the failed window is made again)
     assert s.step_count() == _steps_done(s) == 70
     s.close()
+
+
+def _launches(lib, run):
+    lib.host_calls()
+    run()
+    return lib.host_calls().decode().splitlines()
+
+
+def test_solves_of_the_pair_tests_are_planned_in_pairs(lib):
+    """What test_gpu_pair_paths.py compares with single steps does take pairs."""
+    import pair_cases as PC
+
+    solves = [(PC.lattice(size, bc), []) for size in PC.RAGGED for bc in PC.FACES.values()]
+    for bx, wg in solves:
+        s = H.Solve(lib, bx, wg)
+        s.init()
+        calls = _launches(lib, lambda: s.check(lib.ibmlbm_step(s.h, 12)))
+        assert calls.count("pair 1") == 6 and "collide 1" not in calls, bx
+        s.close()
