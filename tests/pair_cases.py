@@ -15,3 +15,14 @@ RAGGED = [(129, 97, 133), (257, 97, 49), (61, 200, 205)]
 
 def lattice(size, bc):
     return WL.box(*size, bc, 0.6, u_in=(0.03, 0.002, -0.001) if bc[0] != P else (0, 0, 0), rho_out=1.001)
+
+
+def foil(case, complete_case):
+    """Foils and a body force: completed box and wings."""
+    if case == "clap_fling":
+        bx, wg, ph = WL.clap_fling_case()
+    elif case == "cylinder":
+        bx, wg, ph = WL.cylinder_case(nx=257, ny=190, nz=193, d=20.0)
+    else:
+        bx, wg, ph = WL.plate_case(nx=256, ny=192, nz=192, centre=(60.2, 6.4))
+    return complete_case(dict(bx, body_force=[2e-6, -1e-6, 3e-6]), wg, ph)

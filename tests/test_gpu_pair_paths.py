@@ -1,5 +1,6 @@
 """Two steps in one pass against the same steps one by one, bit for bit, where
-a block's column is ragged: a last column of one cell, a last tile of one row.
+a block's column is ragged and on the paths that only some solves take: a last
+column of one cell, a last tile of one row, foils with a body force.
 test_host_api.py checks on the CPU that these solves are planned in pairs."""
 import pytest
 
@@ -20,5 +21,20 @@ def test_ragged_lattice_pairs_equal_single_steps(size, bc):
     for _ in range(11):
         b.step(1)
     _same(a, b)
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("case", ["clap_fling", "cylinder", "plate"])
+def test_foil_and_body_force_pairs_equal_single_steps(case):
+    from paper_2102_01305_amd.solver import complete_case
+
+    bx, wg = PC.foil(case, complete_case)
+    print(f"[pair] {case} with a body force", flush=True)
+    a, b = _solve(bx, wg, 11, step0=210), _solve(bx, wg, 11, step0=210)
+    assert _updates_per_launch(a, lambda: a.step(12)) == 2.0
+    for _ in range(12):
+        b.step(1)
+    _same(a, b, ("u",))
     a.close()
     b.close()

@@ -126,9 +126,11 @@ def _launches(lib, run):
 
 def test_solves_of_the_pair_tests_are_planned_in_pairs(lib):
     """What test_gpu_pair_paths.py compares with single steps does take pairs."""
+    import oracle.params as params
     import pair_cases as PC
 
     solves = [(PC.lattice(size, bc), []) for size in PC.RAGGED for bc in PC.FACES.values()]
+    solves += [PC.foil(c, params.complete_case) for c in ("clap_fling", "cylinder", "plate")]
     for bx, wg in solves:
         s = H.Solve(lib, bx, wg)
         s.init()
