@@ -26,3 +26,25 @@ def foil(case, complete_case):
     else:
         bx, wg, ph = WL.plate_case(nx=256, ny=192, nz=192, centre=(60.2, 6.4))
     return complete_case(dict(bx, body_force=[2e-6, -1e-6, 3e-6]), wg, ph)
+
+
+def batch(complete_case):
+    """(box, wings, storage, check interval, first step, steps alone before the
+    batch) of solves of one batch: lattices, long and short spans, a foil whose
+    neighbours wrap, check steps, 16-bit storage, a body force.  Their windows
+    of 64 steps start at different steps, so that after a while first, second
+    and single steps are taken together."""
+    out = [(lattice((256, 192, 192), FACES["periodic"]), [], "fp32", 0, 0, 0),
+           (lattice((130, 61, 97), FACES["zou_he"]), [], "fp32", 0, 0, 3),
+           (lattice((129, 64, 97), FACES["closed"]), [], "fp32", 0, 0, 2)]
+    for k, (nx, ny, nz, c, sto, check) in enumerate([(64, 48, 8, 8.0, "fp32", 0), (97, 80, 81, 10.0, "fp32", 0),
+                                                     (70, 60, 13, 8.0, "fp32", 0), (160, 128, 128, 16.0, "fp32", 0),
+                                                     (96, 80, 40, 10.0, "fp32", 5), (64, 48, 16, 8.0, "fp16", 0),
+                                                     (128, 96, 60, 12.0, "fp32", 0), (65, 50, 16, 8.0, "fp32", 0)]):
+        bx, wg, ph = WL.clap_fling_case(nx=nx, ny=ny, nz=nz, chord=c)
+        if k == 6:
+            bx = dict(bx, body_force=[2e-6, -1e-6, 3e-6])
+        out.append((*complete_case(bx, wg, ph), sto, check, 40 + k, k % 4))
+    bx, wg, ph = WL.plate_case(nx=70, ny=40, nz=24, centre=(9.0, 9.5))
+    out.append((*complete_case(dict(bx, bc=[P] * 6, u_in=[0.0, 0.0, 0.0]), wg, ph), "fp32", 0, 0, 1))
+    return out

@@ -125,7 +125,8 @@ def _launches(lib, run):
 
 
 def test_solves_of_the_pair_tests_are_planned_in_pairs(lib):
-    """What test_gpu_pair_paths.py compares with single steps does take pairs."""
+    """What test_gpu_pair_paths.py compares with single steps does take pairs:
+    alone, and in a batch with first, second and single steps side by side."""
     import oracle.params as params
     import pair_cases as PC
 
@@ -136,4 +137,19 @@ def test_solves_of_the_pair_tests_are_planned_in_pairs(lib):
         s.init()
         calls = _launches(lib, lambda: s.check(lib.ibmlbm_step(s.h, 12)))
         assert calls.count("pair 1") == 6 and "collide 1" not in calls, bx
+        s.close()
+
+    made = []
+    for bx, wg, storage, check, step0, alone in PC.batch(params.complete_case):
+        made.append(H.Solve(lib, bx, wg, storage=storage, check_interval=check))
+        made[-1].init(step0=step0)
+        made[-1].check(lib.ibmlbm_step(made[-1].h, alone))
+    group = (L.Handle * len(made))(*[s.h for s in made])
+    calls = _launches(lib, lambda: made[0].check(lib.ibmlbm_step_batch(group, len(made), 70)))
+    count = {k: [int(c.split()[1]) for c in calls if c.startswith(k)] for k in ("near", "pair", "collide")}
+    assert max(count["near"]) >= 4 and max(count["pair"]) >= 4 and max(count["collide"]) >= 2
+    alt = [(int(c.split()[1]), int(c.split()[3])) for c in calls if c.startswith("markers")]
+    assert len({m for n, m in alt if n >= 4 and 0 < m < (1 << n) - 1}) >= 4   # groups with both kinds of source
+    for s, (_, _, _, _, step0, alone) in zip(made, PC.batch(params.complete_case)):
+        assert s.step_count() - step0 == _steps_done(s) == 70 + alone
         s.close()
