@@ -67,6 +67,14 @@ constexpr int kSlots = 8;
 constexpr size_t kSlotBytes = size_t(2) << 20;
 constexpr int kPoolSlots = 32;     // of all handles together: four transfers at once
 
+// Up to this size a transfer is left to the kernel that lays the values out,
+// which reads or writes the pinned slot itself: a copy between costs 16 to 20 us
+// of latency, more than the slower access through the link up to 1 MB.
+// u / f up / f down in us, by copy and by kernel: 16x16x8 36 / 51 / 45 and
+// 19 / 31 / 28; 32x16x16 41 / 75 / 69 and 23 / 58 / 53; 64x32x32 74 and 62 (f is
+// past the limit); 64x64x32 (2 MB) rho 63 and 74.
+constexpr size_t kDirectBytes = size_t(1) << 20;
+
 // Pinned staging of one thread of a transfer, with an event of one device.
 struct Slot {
   void* buf = nullptr;
@@ -904,24 +912,54 @@ struct DeviceScope {
   }
 };
 
-// Move n floats between `dev` and the host on h's stream, chunk by chunk:
+// (of the stream, in a DeviceScope)
+int current_device() {
+  int d = 0;
+  return hipGetDevice(&d) == hipSuccess ? d : 0;
+}
+
+// Up to `want` slots for the length of a scope (none for handles that must not
+// allocate).
+struct Borrowed {
+  Slot slot[kSlots];
+  int n = 0;
+  Borrowed(ibmlbm_t h, int want, int device) {
+    if (!h->noalloc && want > 0) n = slot_pool().borrow(slot, want, device);
+  }
+  ~Borrowed() { slot_pool().give_back(slot, n); }
+};
+
+// Where the kernel that lays out n floats for a transfer puts (or finds) them:
+// `dev`, from or to which `staged` copies, or, where they are few, a pinned
+// slot itself, which leaves nothing to copy.
+struct Dense {
+  Borrowed slot;
+  bool direct;
+  float* at;
+  Dense(ibmlbm_t h, float* dev, size_t n) : slot(h, n * sizeof(float) <= kDirectBytes, current_device()) {
+    direct = slot.n > 0;
+    at = direct ? static_cast<float*>(slot.slot[0].buf) : dev;
+  }
+};
+
+// Move n floats between d.at + first and the host on h's stream, chunk by chunk:
 // fn(begin, count, buf) fills buf before its upload (up) or takes it after its
 // download.  Returns when all are moved.
 template <class F>
-int staged(ibmlbm_t h, float* dev, size_t n, bool up, const F& fn) {
+int staged(ibmlbm_t h, const Dense& d, size_t first, size_t n, bool up, const F& fn) {
   const size_t chunk = kSlotBytes / sizeof(float), chunks = (n + chunk - 1) / chunk;
   if (n == 0) return IBMLBM_OK;
+  float* const dev = d.at + first;
+  if (d.direct) {
+    if (!up) HIP_TRY(h, hipStreamSynchronize(h->stream));
+    fn(0, n, dev);
+    return IBMLBM_OK;
+  }
   const unsigned cores = std::max(1u, std::thread::hardware_concurrency());
-  int device = 0;                                      // (of the stream: the entry points make it current)
-  HIP_TRY(h, hipGetDevice(&device));
+  const int device = current_device();
   const int want = (int)std::min<size_t>({chunks, (size_t)kSlots, (size_t)cores});
-  struct Borrowed {
-    Slot slot[kSlots];
-    int n = 0;
-    ~Borrowed() { slot_pool().give_back(slot, n); }
-  } borrowed;
+  Borrowed borrowed(h, want, device);
   Slot* const slot = borrowed.slot;
-  if (!h->noalloc) borrowed.n = slot_pool().borrow(slot, want, device);
   const int have = borrowed.n;
   std::vector<float> plain;                            // staging where there is no pinned memory
   if (have == 0) {
@@ -1336,14 +1374,19 @@ int ibmlbm_init_fields(ibmlbm_t h, const double* rho, const double* u, const dou
   const size_t N = L.N;
   h->cur_is_A = true;
   void* dst = h->ws + L.fA.off;
+  // the ghost records, behind the kernels of the cells; when all have ended
+  auto finish = [&] {
+    const hipError_t e = launch_ghost(h->cfg.storage, h->geo, h->phys, dst, h->stream);
+    return e == hipSuccess ? hipStreamSynchronize(h->stream) : e;
+  };
   if (fdist) {
     // f_i - w_i of as many populations as the other state buffer holds, dense
     // in floats there, then into the padded layout in the stored type
-    float* dense = reinterpret_cast<float*>(h->ws + L.fB.off);
-    const int most = dense_populations(h);
+    const Dense dense(h, reinterpret_cast<float*>(h->ws + L.fB.off), kQ * N);
+    const int most = dense.direct ? kQ : dense_populations(h);
     for (int q0 = 0; q0 < kQ; q0 += most) {
       const int nq = std::min(most, kQ - q0);
-      int rc = staged(h, dense, (size_t)nq * N, true, [&](size_t begin, size_t count, float* buf) {
+      int rc = staged(h, dense, 0, (size_t)nq * N, true, [&](size_t begin, size_t count, float* buf) {
         for (size_t k = 0; k < count;) {
           const size_t i = (size_t)q0 * N + begin + k, q = i / N, run = std::min(count - k, (q + 1) * N - i);
           const double w = weight((int)q);
@@ -1352,9 +1395,9 @@ int ibmlbm_init_fields(ibmlbm_t h, const double* rho, const double* u, const dou
         }
       });
       if (rc) return rc;
-      HIP_TRY(h, launch_pack(h->cfg.storage, h->geo, dense, q0, nq, dst, h->stream));
+      HIP_TRY(h, launch_pack(h->cfg.storage, h->geo, dense.at, q0, nq, dst, h->stream));
     }
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    HIP_TRY(h, finish());
   } else {
     // stage FP64 rho and u in the other state buffer (free between steps)
     double* stage = reinterpret_cast<double*>(h->ws + L.fB.off);
@@ -1365,10 +1408,8 @@ int ibmlbm_init_fields(ibmlbm_t h, const double* rho, const double* u, const dou
     if (rho) HIP_TRY(h, hipMemcpyAsync(drho, rho, N * 8, hipMemcpyHostToDevice, h->stream));
     if (u) HIP_TRY(h, hipMemcpyAsync(du, u, 3 * N * 8, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(h, launch_init_eq(h->cfg.storage, h->geo, drho, du, dst, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    HIP_TRY(h, finish());
   }
-  HIP_TRY(h, launch_ghost(h->cfg.storage, h->geo, h->phys, dst, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
   h->step = step0;
   h->initialized = true;
   h->markers_valid = false;
@@ -1519,20 +1560,20 @@ int ibmlbm_fields(ibmlbm_t h, int32_t which, double* out) {
   const LatticeLayout& L = h->L;
   const size_t N = L.N;
   if (which == IBMLBM_FIELD_RHO || which == IBMLBM_FIELD_U) {
-    float* scratch = static_cast<float*>(next_state(h));
-    HIP_TRY(h, launch_moments(h->cfg.storage, h->geo, h->phys, cur_state(h), scratch, h->stream));
+    const Dense dense(h, static_cast<float*>(next_state(h)), 4 * N);
+    HIP_TRY(h, launch_moments(h->cfg.storage, h->geo, h->phys, cur_state(h), dense.at, h->stream));
     const bool u = which == IBMLBM_FIELD_U;
-    return staged(h, u ? scratch + N : scratch, u ? 3 * N : N, false, [&](size_t begin, size_t count, const float* buf) {
+    return staged(h, dense, u ? N : 0, u ? 3 * N : N, false, [&](size_t begin, size_t count, const float* buf) {
       for (size_t j = 0; j < count; ++j) out[begin + j] = buf[j];
     });
   }
   if (which != IBMLBM_FIELD_FDIST) return fail(h, IBMLBM_EINVAL, "unknown field %d", which);
-  float* dense = static_cast<float*>(next_state(h));
-  const int most = dense_populations(h);
+  const Dense dense(h, static_cast<float*>(next_state(h)), kQ * N);
+  const int most = dense.direct ? kQ : dense_populations(h);
   for (int q0 = 0; q0 < kQ; q0 += most) {
     const int nq = std::min(most, kQ - q0);
-    HIP_TRY(h, launch_unpack(h->cfg.storage, h->geo, cur_state(h), q0, nq, dense, h->stream));
-    int rc = staged(h, dense, (size_t)nq * N, false, [&](size_t begin, size_t count, const float* buf) {
+    HIP_TRY(h, launch_unpack(h->cfg.storage, h->geo, cur_state(h), q0, nq, dense.at, h->stream));
+    int rc = staged(h, dense, 0, (size_t)nq * N, false, [&](size_t begin, size_t count, const float* buf) {
       for (size_t k = 0; k < count;) {
         const size_t i = (size_t)q0 * N + begin + k, q = i / N, run = std::min(count - k, (q + 1) * N - i);
         const double w = weight((int)q);

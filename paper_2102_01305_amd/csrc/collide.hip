@@ -273,7 +273,8 @@ hipError_t launch_moments(int storage, const Geo& g, const Phys& p, const void* 
 }
 
 // Checkpoints: the stored populations as dense float planes of f - w, and
-// back, one thread per cell (reads and writes run along x in both).
+// back, one thread per cell (reads and writes run along x in both).  All its
+// reads are issued together: for a small field `dense` is host memory.
 template <class St, bool PACK>
 __global__ void k_dense(Geo g, float* dense, int q0, int nq, typename St::T* state) {
   const size_t N = (size_t)g.nx * g.ny * g.nz;
@@ -283,12 +284,17 @@ __global__ void k_dense(Geo g, float* dense, int q0, int nq, typename St::T* sta
   const size_t r = cell / g.nx;
   const int y = (int)(r % g.ny), z = (int)(r / g.ny);
   typename St::T* own = state + rowbase(g, y, z) + x;
-  for (int q = 0; q < nq; ++q) {
-    typename St::T* p = own + (long long)(q0 + q) * g.ps;
+  float v[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q)
+    if (q < nq) v[q] = PACK ? dense[q * N + cell] : St::ld(own + (long long)(q0 + q) * g.ps);
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    if (q >= nq) continue;
     if (PACK)
-      St::st(p, dense[q * N + cell]);
+      St::st(own + (long long)(q0 + q) * g.ps, v[q]);
     else
-      dense[q * N + cell] = St::ld(p);
+      dense[q * N + cell] = v[q];
   }
 }
 

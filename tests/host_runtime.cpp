@@ -42,6 +42,7 @@ Stream null_stream[2];
 long long pinned = 0, pinned_most = 0;
 std::map<void*, size_t> pins;
 std::vector<std::string> calls;
+int copies = 0;
 std::string fail_kind;
 int fail_after = 0;
 
@@ -98,6 +99,7 @@ __attribute__((visibility("default"))) void host_fail(const char* kind, int afte
   fail_kind = kind;
   fail_after = after;
 }
+__attribute__((visibility("default"))) int host_copies() { return copies; }
 // The launches since the last call, one a line.
 __attribute__((visibility("default"))) const char* host_calls() {
   static std::string text;
@@ -160,6 +162,7 @@ hipError_t hipStreamSynchronize(hipStream_t st) {
 }
 hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind, hipStream_t st) {
   std::lock_guard<std::recursive_mutex> l(mu);
+  ++copies;
   if (find(st)->work.empty())
     std::memcpy(to, from, n);
   else

@@ -51,6 +51,14 @@ def test_checkpoint_round_trip(size, storage):
     s.close()
 
 
+@pytest.mark.parametrize("storage", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("size", [(27, 73, 7), (69, 200, 1), (64, 32, 32), (64, 33, 32)])
+def test_transfers_by_kernel_and_by_copies(size, storage):
+    """Either side of the 1 MB up to which the kernels read and write host
+    memory: 13797 cells of 19 values, 65536 of 4."""
+    test_checkpoint_round_trip(size, storage)
+
+
 @pytest.mark.parametrize("history", [7, 600, 2000])
 def test_force_rows_by_kernel_and_by_copies(history):
     print(f"[transfer] force rows, ring of {history}", flush=True)

@@ -83,6 +83,18 @@ def test_pinned_staging_is_bounded_for_all_solves_and_given_back(lib):
     assert lib.host_pinned(0) == 0
 
 
+@pytest.mark.parametrize("size,copied", [((4, 4, 1), False), ((27, 73, 7), False), ((69, 200, 1), True)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else None)
+def test_small_transfers_make_no_copy(lib, size, copied):
+    """Up to 1 MB (13797 cells for the populations) the kernel itself reads or
+    writes the pinned slot."""
+    s = H.Solve(lib, WL.box(*size, [P] * 6, 0.6), stream=H.PER_THREAD)
+    before = lib.host_copies()
+    _transfers(s)
+    assert (lib.host_copies() > before) == copied
+    s.close()
+
+
 def _foil_solve(lib, nx=256, ny=192, nz=192, chord=20.0, step0=0, **kw):
     import oracle.params as params
 
