@@ -70,7 +70,10 @@ struct FoilBox {
   const unsigned* bits;
 };
 
-struct CollideArgs {
+// On a cache line of its own for every step: a step's arguments are cold when
+// its kernel starts, and each further line that the first waves wait for costs
+// a launch 0.3 us (256x256x13 25.8 us, 26.1 with arguments across lines).
+struct alignas(64) CollideArgs {
   Geo g;
   Phys p;
   int nw;                    // foils whose correction the kernel applies
