@@ -68,7 +68,9 @@ __device__ __forceinline__ void collide_block(const CollideArgs& __restrict__ a,
     // Bijective on the tiles; grouped launches keep the plain order.
     int lt = lb;
     const int G = (a.nxc >= 8 ? 8 : 4) * a.nxc;
-    const int M = a.nblocks / (8 * G) * 8 * G;
+    // (M from gridDim, which loads beside the arguments' address: from nblocks,
+    // its load came behind a branch, 0.2 us more a launch)
+    const int M = (int)(gridDim.x / (8 * G)) * 8 * G;
     if (lt < M && (int)gridDim.x == a.nblocks) {
       const int xcd = lt & 7, k = lt >> 3;
       lt = ((k / G) * 8 + xcd) * G + k % G;
