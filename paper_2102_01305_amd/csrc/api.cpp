@@ -767,10 +767,11 @@ int record_event(ibmlbm_t h, hipStream_t st, int kind, bool start, double cells 
   return IBMLBM_OK;
 }
 
-// Arguments of step s: the parts that
-// never change for this handle, then the step's own (time, window slot, force-history row, node boxes and the grids they imply).
 const void* dev_ma(ibmlbm_t h, int slot);
 
+// Arguments of step s: the parts that never change for this handle, then the
+// step's own (time, window slot, force-history row, node boxes and the grids
+// they imply).
 void step_args(ibmlbm_t h, long long s, CollideArgs& ca, MarkerArgs& ma) {
   const LatticeLayout& L = h->L;
   const ibmlbm_config& c = h->cfg;

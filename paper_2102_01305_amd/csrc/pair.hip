@@ -128,12 +128,12 @@ __device__ __forceinline__ void correction2(const Geo& g, const CollideArgs& a, 
 }
 
 // A block takes a column of the lattice, 64 cells along x times R = 12 rows
-// along z, and marches along y over `ylen` planes.  At plane p its 15 waves (one row
-// each, two of them the rows beside the column, and one wave of lanes for the
-// cells beside it in x) have step s's pull of that plane in registers, update
-// it and exchange the result through LDS; the R rows then have every value that
-// step s+1 of plane p-1 pulls: from plane p just exchanged, and from planes p-1
-// and p-2 in the registers of the lane that uses them.
+// along z, and marches along y over `ylen` planes.  At plane p its 15 waves (one
+// row each, two of them the rows beside the column, and one wave of lanes for
+// the cells beside it in x) have step s's pull of that plane in registers,
+// update it and exchange the result through LDS; the R rows then have every
+// value that step s+1 of plane p-1 pulls: from plane p just exchanged, and from
+// planes p-1 and p-2 in the registers of the lane that uses them.
 //
 // Bound: memory, as for one step at a time, but the lattice is read and
 // written once for two steps: per launch 1.12 x the 76 B a cell that a read
@@ -142,16 +142,23 @@ __device__ __forceinline__ void correction2(const Geo& g, const CollideArgs& a, 
 // units busy 41% of the time.  Two steps of the collide kernel against one
 // launch here: 256x192x192 483 -> 317 us, 256x256x256 864 -> 592,
 // 512x384x384 3926 -> 2415; clap & fling 256x192x192 335 us (a plane that meets
-// a foil takes 2.4 us longer), whole step 275 -> 207 us.
-// Why this shape: one block per compute unit, so R as large as 16 waves and
-// 160 KB of LDS allow (halo work 1 + 3/R; 12 divides the spans in use); the
-// same with R = 7 or 8 and two blocks per unit 1262-1281 us a step at
-// 512x384x384 (1228 with R = 12), R = 5 at 128 registers 1328, R = 13 1269.
+// a foil takes 2.4 us longer), whole step 275 -> 207 us.  Where memory does not
+// bind, a plane takes 3.8 us of issue, to which scalar pressure adds: 127 to 316
+// scalar registers are kept in lanes of vector registers, and most of the lane
+// reads that bring them back (553 of 564 with foils) lie in the march.
+// Why this shape: one block per compute unit, so R near what 16 waves and
+// 160 KB of LDS allow (halo work 1 + 3/R); the same with R = 7 or 8 and two
+// blocks per unit 1262-1281 us a step at 512x384x384 (1228 with R = 12), R = 5
+// at 128 registers 1328.  R = 13, with all 16 waves, is slower by 3% where 12
+// divides the span (256x192x192 160.6 -> 165.9 us a step, 512x384x384 1228 ->
+// 1269) and faster where its tiles are fewer (257x97x65 42.6 -> 38.1,
+// 256x192x101 92.7 -> 91.5, 256x192x193 180.7 -> 166.6, 256x192x199 183.7 ->
+// 169.2): 12 is not the better one everywhere.
 // What the march needed: descriptors per z in place of per-lane addresses, no
-// row offsets kept over the loop (168 registers and spills with them, 103-128
-// now; a spilled one's reload in the march waits for the pull), the next plane's
-// pull in flight over the exchange and step s+1 (1427 -> 1284 us a step), and LDS by plane parity, one barrier a plane
-// instead of two (-> 1254).
+// row offsets kept over the loop (168 vector registers and spills with them,
+// 103-128 now and none in memory; a reload in the march waits for the pull), the
+// next plane's pull in flight over the exchange and step s+1 (1427 -> 1284 us a
+// step), and LDS by plane parity, one barrier a plane instead of two (-> 1254).
 template <bool IBM, bool FORCE, bool ZH>
 __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, const CollideArgs& __restrict__ b,
                                            int lb, int nblocks, int ylen, const void* src, void* dst) {
@@ -279,8 +286,8 @@ __device__ __forceinline__ void pair_block(const CollideArgs& __restrict__ a, co
   // (in the waves of the rows, one lane of 64 took them a third of their time).
   auto ghosts = [&](int q) {
     // With foils and a body force, what follows is made anew for each plane:
-    // kept over the loop it spilled two registers, whose reloads in the march
-    // wait for the pull in flight (clap & fling 256 x 192 x 192 with a body
+    // kept over the loop it spilled two vector registers to memory, whose
+    // reloads in the march wait for the pull in flight (clap & fling 256 x 192 x 192 with a body
     // force 222 -> 212 us a step; the other instantiations, which do not spill,
     // 0.5% slower by it).
     int ln = lane;
