@@ -93,10 +93,11 @@ def collide_source_hash():
 
 
 def measured_traffic(name, storage):
-    """HBM bytes per collide launch from the counter summary under profiles/
+    """HBM bytes per launch of the lattice kernel (k_collide, or k_pair where
+    steps are taken in pairs) from the counter summary under profiles/
     (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy of known size), or None
     when there is none for this workload or the collide sources changed since."""
-    path = os.path.join(ROOT, "profiles", f"k_collide_{name}_{storage}_traffic.md")
+    path = os.path.join(ROOT, "profiles", f"lattice_traffic_{name}_{storage}.md")
     if not os.path.exists(path):
         return None
     kv = {}
@@ -380,7 +381,10 @@ def main():
                      "timed_launches": fig["launches"],
                      "marker_ms_per_step": round(fig["marker_ms"], 5),
                      "copy_gbs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4)},
+        # bytes of one step at a time (the lattice read and written once a step),
+        # also where a launch takes two steps and moves half of that a step
         "hbm_frac_whole_step": round(mlups * 1e6 * bpc / (HBM_PEAK_GBS * 1e9), 4),
+        "hbm_frac_whole_step_moved": round(mlups * 1e6 * bpc / fig["steps_per_launch"] / (HBM_PEAK_GBS * 1e9), 4),
     }
     if not args.no_variants and args.workload == "cf" and args.storage == "fp32":
         # the same measurement for the 16-bit storages and the largest
