@@ -23,7 +23,7 @@
  *    ibmlbm_workspace_bytes() bytes, 256-byte aligned, handed to create().
  *    The library never allocates device memory.  The library owns only the
  *    host-side handle and pinned host memory: per handle a small buffer
- *    (about 210 KB) through which it uploads the launch arguments of 64 steps
+ *    (about 220 KB) through which it uploads the launch arguments of 64 steps
  *    at a time and returns force rows, and, for the calls that move a whole
  *    field, staging that all handles of the process share (16 MB for one such
  *    call at a time, at most 64 MB), given back with the last handle.  Input
