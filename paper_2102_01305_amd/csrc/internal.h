@@ -70,10 +70,13 @@ struct FoilBox {
   const unsigned* bits;
 };
 
-// On a cache line of its own for every step: a step's arguments are cold when
-// its kernel starts, and each further line that the first waves wait for costs
-// a launch 0.3 us (256x256x13 25.8 us, 26.1 with arguments across lines).
-struct alignas(64) CollideArgs {
+// Of whole cache lines, so that every step's arguments start on one: they are
+// cold when its kernel starts, and each further line that the first waves wait
+// for costs a launch 0.1 us.  (By its size, not by alignas: loads that the
+// compiler knows to be aligned get wider and want longer runs of scalar
+// registers, and the two-step kernels with a body force kept 5 to 170 more of
+// them in lanes: 257x97x65 with a force 42.6 -> 43.3 us a step.)
+struct CollideArgs {
   Geo g;
   Phys p;
   int nw;                    // foils whose correction the kernel applies
@@ -92,7 +95,9 @@ struct alignas(64) CollideArgs {
   long long hist_row;
   double qS;                 // 0.5 u_ref^2 area_ref
   double sense[kMaxWings], chord[kMaxWings];
+  double pad[3];
 };
+static_assert(sizeof(CollideArgs) % 64 == 0, "a step's arguments start on a cache line");
 
 // Cells around a foil that step s + 1's marker kernels pull from: its node box
 // of that step, which reaches past every neighbour of a support node by a
