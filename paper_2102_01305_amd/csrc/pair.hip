@@ -143,7 +143,7 @@ __device__ __forceinline__ void correction2(const Geo& g, const CollideArgs& a, 
 // launch here: 256x192x192 483 -> 317 us, 256x256x256 864 -> 592,
 // 512x384x384 3926 -> 2415; clap & fling 256x192x192 335 us (a plane that meets
 // a foil takes 2.4 us longer), whole step 275 -> 207 us.  Where memory does not
-// bind, a plane takes 3.8 us of issue, to which scalar pressure adds: 127 to 316
+// bind, a plane takes 3.8 us of issue, to which scalar pressure adds: 127 to 312
 // scalar registers are kept in lanes of vector registers, and most of the lane
 // reads that bring them back (553 of 564 with foils) lie in the march.
 // Why this shape: one block per compute unit, so R near what 16 waves and
