@@ -25,8 +25,8 @@
  *    host-side handle and pinned host memory: per handle a small buffer
  *    (about 220 KB) through which it uploads the launch arguments of 64 steps
  *    at a time and returns force rows, and, for the calls that move a whole
- *    field, staging that all handles of the process share (16 MB for one such
- *    call at a time, at most 64 MB), given back with the last handle.  Input
+ *    field, staging that all handles of the process share (16 MB a handle, at
+ *    most 64 MB in all), given back with the last handle.  Input
  *    arrays are copied, never retained.
  *  - Work is enqueued on the caller's HIP stream (hipStream_t passed as
  *    void*; NULL = the null stream).  step() only enqueues; forces(),

@@ -118,6 +118,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "an error of the stand-in"; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   std::lock_guard<std::recursive_mutex> l(mu);
+  if (fail_kind == "pinned" && fail_after-- <= 0) return hipErrorOutOfMemory;   // from then on
   *p = std::malloc(n);
   pins[*p] = n;
   pinned += (long long)n;

@@ -60,9 +60,9 @@ def test_pinned_staging_is_bounded_for_all_solves_and_given_back(lib):
     assert lib.host_pinned(0) == 0
     made = [H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6), stream=lib.host_stream(0)) for _ in range(8)]
     handles = lib.host_pinned(0)                       # what each handle holds for its launch arguments
-    for s in made[:3]:
+    for s in made:
         _transfers(s)
-    assert lib.host_pinned(0) - handles <= 16 << 20    # one after the other: the staging of one transfer
+    assert lib.host_pinned(0) - handles <= 64 << 20
     errors = []
 
     def go(s):
@@ -79,6 +79,25 @@ def test_pinned_staging_is_bounded_for_all_solves_and_given_back(lib):
     assert not errors
     assert lib.host_pinned(1) - handles <= 64 << 20    # however many at once
     for s in made:
+        s.close()
+    assert lib.host_pinned(0) == 0
+    one = H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6))
+    handles = lib.host_pinned(0)
+    _transfers(one)
+    _transfers(one)
+    assert lib.host_pinned(0) - handles <= 16 << 20    # a single solve: the staging of one transfer
+    one.close()
+    assert lib.host_pinned(0) == 0
+
+
+@pytest.mark.parametrize("slots", [0, 1, 3])
+def test_transfers_without_pinned_memory_left(lib, slots):
+    solves = [H.Solve(lib, WL.box(130, 70, 69, [P] * 6, 0.6), stream=lib.host_stream(0)) for _ in range(2)]
+    lib.host_fail(b"pinned", slots)
+    for s in solves + solves:
+        _transfers(s)
+    lib.host_fail(b"", 0)
+    for s in solves:
         s.close()
     assert lib.host_pinned(0) == 0
 
